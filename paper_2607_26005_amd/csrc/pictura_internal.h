@@ -19,6 +19,13 @@ struct WorldGrid {
     int32_t pad0, pad1;
 };
 
+// A view tile's framebuffer: roundup8(h) rows of roundup8(w) + 4 words in LDS
+// (whole 8x8 blocks and four words for the record ring).  kTileWords is 64x64's,
+// with which eight workgroups of two waves fill a CU's LDS and its registers.
+constexpr int kTileWords = 64 * 68;
+constexpr int kTileMax = 128;   // most columns or rows
+inline constexpr int tile_words(int w, int h) { return (((w + 7) & ~7) + 4) * ((h + 7) & ~7); }
+
 // The binned unit is a primitive: one triangle (a, b, c), or a pair of input
 // triangles (a, b, c), (a, c, d) that share the edge a-c and the class (a quad
 // split along a diagonal: the generators' ground tiles, road segments,

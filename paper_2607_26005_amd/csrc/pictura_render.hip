@@ -72,9 +72,9 @@ constexpr int kThreads = 64 * kViewWaves;
 constexpr int kWavesPerSimd = 4;  // register budget: four waves per SIMD (as many as the LDS admits)
 constexpr int kSmallPx = PICTURA_SMALL_PX;   // pieces with at most this many bounding-box pixels take the packed raster
 constexpr int kQueue = 192;       // per-wave queue of first-pass survivors
-// Framebuffer rows are padded to a pitch of 4 mod 32 words, so the 64 lanes
-// of an 8x8 block hit every LDS bank exactly twice.
-constexpr int kFbCap = 64 * 68;
+// The framebuffer holds whole 8x8 blocks, rows padded to a pitch of 4 mod 8
+// words, so the 64 lanes of a block spread evenly over the LDS banks.
+constexpr int kFbCap = kTileWords;
 static_assert(kViewWaves == 1 || kViewWaves == 2 || kViewWaves == 4, "1, 2 or 4 waves per view tile");
 
 struct Cam {
@@ -672,22 +672,23 @@ __device__ __forceinline__ void raster_packed(const RenderParams& P, Shared& S, 
 }
 
 // Rasterize one record with the whole wave.  Lane b tests 8x8 block b of
-// the bounding box (a tile has at most 8 x 8 blocks): the edge value at the
-// block corner that maximises it must be >= 0 for all three edges.  The
-// passing blocks are then rasterized one per step, lane l handling pixel
-// (l & 7, l >> 3): its edge values at that pixel of block (0, 0) plus the
-// block's offsets, which the lane that tested the block computed.
+// the bounding box (kWide: 64 of them at a time; else a tile has at most 8 x
+// 8): the edge value at the block corner that maximises it must be >= 0 for
+// all three edges.  The passing blocks are then rasterized one per step, lane
+// l handling pixel (l & 7, l >> 3): its edge values at that pixel of block (0,
+// 0) plus the block's offsets, which the lane that tested the block computed.
 //
 // int32 path (I32): the scaled edge floor(E / 256) with |dx|, |dy| < 2^22 and
 // |floor(c / 256)| < 2^30, so dx, dy fit a 24-bit multiply and the value stays
-// below 2^30 + 2 * 63 * 2^22 < 2^31 anywhere in the tile.
-// fp64 path: |a_k|, |b_k| <= 2^38, so with tile coordinates below 64 every
+// below 2^30 + 2 * 127 * 2^22 < 2^31 over 128 x 128 pixels, more than any tile.
+// fp64 path: |a_k|, |b_k| <= 2^38, so with tile coordinates below 128 every
 // product and partial sum is an exact integer when |c| < 2^52; otherwise |c|
-// exceeds the sum of all other terms by 2^9 and fixes the sign of every sum.
-// Fast: the tile is a whole number of blocks and pixel-centre offsets are
-// exact sums (P.pix_exact), so no lane leaves the tile and the offset of a
-// pixel centre is the lane's own plus the block's.
-template <bool I32, bool Fast>
+// exceeds the sum of all other terms by 2^5 and fixes the sign of every sum.
+// Fast: pixel-centre offsets are exact sums (P.pix_exact), so the offset of a
+// pixel centre is the lane's own plus the block's.  Lanes of a block that
+// leave the tile write framebuffer words that no one reads (it holds whole
+// blocks, and the record ring keeps to the four words behind them).
+template <bool I32, bool Fast, bool kWide>
 __device__ __forceinline__ void raster_blocks(const RenderParams& P, Shared& S, const Tile& T, const uint32_t* u,
                                               float pa, float pb, float pc, uint32_t box, uint32_t j1w,
                                               float pxl, float pyl, int loff4)
@@ -700,7 +701,10 @@ __device__ __forceinline__ void raster_blocks(const RenderParams& P, Shared& S, 
     const int bx0 = i0 >> 3, by0 = j0 >> 3;
     const int nbx = (i1 >> 3) - bx0 + 1, nb = nbx * ((j1 >> 3) - by0 + 1);
     // b / nbx == (b * rinv) >> 16 for b < 64 and nbx <= 8
-    const uint32_t rinv = nbx == 1 ? 65536u : nbx == 2 ? 32768u : nbx == 3 ? 21846u : nbx == 4 ? 16384u
+    // (kWide: b < 256 and nbx <= 16, the quotient rounded down plus 1)
+    constexpr int kMask = kWide ? 15 : 7;
+    const uint32_t rinv = kWide ? (uint32_t)(65536.0f * __builtin_amdgcn_rcpf((float)nbx)) + 1u
+                        : nbx == 1 ? 65536u : nbx == 2 ? 32768u : nbx == 3 ? 21846u : nbx == 4 ? 16384u
                         : nbx == 5 ? 13108u : nbx == 6 ? 10923u : nbx == 7 ? 9363u : 8192u;
     E A[3], B[3], Cc[3], Eb[3], off[3];
 #pragma unroll
@@ -717,12 +721,14 @@ __device__ __forceinline__ void raster_blocks(const RenderParams& P, Shared& S, 
             Eb[k] = fma(A[k], (double)lx, fma(B[k], (double)ly, Cc[k]));
         }
     }
-    // lane b: block b of the box
-    const int eby = (int)(((uint32_t)lane * rinv) >> 16), ebx = lane - eby * nbx;
-    // (lanes past the box hold no block; the masks keep X and Y below 64, so the
+    for (int b0 = 0;; b0 += 64) {
+    // lane b: block b0 + b of the box
+    const int bi = b0 + lane;
+    const int eby = (int)(((uint32_t)bi * rinv) >> 16), ebx = bi - eby * nbx;
+    // (lanes past the box hold no block; the masks keep X and Y small, so the
     // products below stay 24-bit multiplies)
-    const int X = ((bx0 + ebx) & 7) * 8, Y = ((by0 + eby) & 7) * 8;
-    bool pass = lane < nb;
+    const int X = ((bx0 + ebx) & kMask) * 8, Y = ((by0 + eby) & kMask) * 8;
+    bool pass = bi < nb;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         if constexpr (I32) {
@@ -740,7 +746,7 @@ __device__ __forceinline__ void raster_blocks(const RenderParams& P, Shared& S, 
     const uint32_t boff = (uint32_t)((Y * T.pitch + X) * 4);   // byte offset of the block in the framebuffer
     uint64_t m = __ballot(pass);
     if (P.stats && lane == 0) {
-        atomicAdd(&S.stat[kStBlocksTested], (uint32_t)nb);
+        if (b0 == 0) atomicAdd(&S.stat[kStBlocksTested], (uint32_t)nb);
         atomicAdd(&S.stat[kStBlocksPassed], (uint32_t)__popcll(m));
     }
     // Lanes that miss the piece take the key 0xFFFFFFFF, which changes
@@ -799,6 +805,8 @@ __device__ __forceinline__ void raster_blocks(const RenderParams& P, Shared& S, 
         uint32_t a0;
         const uint32_t k0 = key_at(b0, a0);
         atomicMin((uint32_t*)((char*)S.fb + a0), k0);
+    }
+    if (!kWide || b0 + 64 >= nb) break;
     }
 }
 
@@ -989,6 +997,7 @@ __device__ __forceinline__ void aa_packed(const RenderParams& P, Shared& S, Wave
 // triangle (a, b, c) in either orientation, or with q4 the 4-gon (a, b, c, d)
 // in positive orientation; a triangle's fourth edge is a constant c_3 = 1
 // that its coverage does not use.
+template <bool kWide>
 __device__ void aa_pieces(const RenderParams& P, Shared& S, WaveLds& L, uint32_t* fbo, const Tile& T, bool ok, bool q4, int ax,
                           int ay, int bx, int by, int cx, int cy, int dx4, int dy4, float pa, float pb, float pc,
                           uint32_t cls)
@@ -1065,14 +1074,18 @@ __device__ void aa_pieces(const RenderParams& P, Shared& S, WaveLds& L, uint32_t
         }
         const float rpa = readlane_f(pa, l), rpb = readlane_f(pb, l), rpc = readlane_f(pc, l);
         const uint32_t rcls = readlane(cls, l);
-        const int nbx = (ri1 - ri0 + 8) >> 3, nby = (rj1 - rj0 + 8) >> 3;   // at most 8 x 8 blocks
+        // blocks of the window, 8 x 8 of them at a time (not kWide: that is all)
+        for (int gj = rj0;; gj += 64) {
+        for (int gi = ri0;; gi += 64) {
+        const int nbx = kWide ? min((ri1 - gi + 8) >> 3, 8) : (ri1 - gi + 8) >> 3;
+        const int nby = kWide ? min((rj1 - gj + 8) >> 3, 8) : (rj1 - gj + 8) >> 3;
         uint64_t bm = 1;
         if (nbx * nby > 1) {
             // lane = block (lx, ly) of the window: does it hold a fragment?
             bool need = false;
             if (lx < nbx && ly < nby) {
-                const int bi0 = ri0 + 8 * lx, bi1 = min(bi0 + 7, ri1);
-                const int bj0 = rj0 + 8 * ly, bj1 = min(bj0 + 7, rj1);
+                const int bi0 = gi + 8 * lx, bi1 = min(bi0 + 7, ri1);
+                const int bj0 = gj + 8 * ly, bj1 = min(bj0 + 7, rj1);
                 bool out = false, in = true;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
@@ -1091,7 +1104,7 @@ __device__ void aa_pieces(const RenderParams& P, Shared& S, WaveLds& L, uint32_t
         while (bm) {
             const int b = __builtin_ctzll(bm);
             bm &= bm - 1;
-            const int i = ri0 + 8 * (b & 7) + lx, j = rj0 + 8 * (b >> 3) + ly;   // tile pixel
+            const int i = gi + 8 * (b & 7) + lx, j = gj + 8 * (b >> 3) + ly;   // tile pixel
             if (i > ri1 || j > rj1) continue;
             const double di = (double)i, dj = (double)j;
             const uint32_t f = aa_fragment(P, rq4, aa_cover(fma(rsy[0], dj, fma(rsx[0], di, re[0])), rr[0]),
@@ -1103,10 +1116,14 @@ __device__ void aa_pieces(const RenderParams& P, Shared& S, WaveLds& L, uint32_t
             STAT(kStAaFrags, f != 0xFFFFFFFFu ? 1 : 0);
             if (f != 0xFFFFFFFFu) atomicMin(&fbo[j * P.W + i], f);
         }
+        if (!kWide || gi + 64 > ri1) break;
+        }
+        if (!kWide || gj + 64 > rj1) break;
+        }
     }
 }
 
-template <bool kAA, bool kHasLights>
+template <bool kAA, bool kHasLights, bool kWide>
 __device__ __forceinline__ void exact_pass(const RenderParams& P, Shared& S, WaveLds& L, const Tile& T, const Cam& cam,
                                            bool live, uint32_t entry, int64_t abase_w, int64_t lbase_w, float pxl,
                                            float pyl, int loff4, uint32_t* fbo)
@@ -1304,10 +1321,10 @@ __device__ __forceinline__ void exact_pass(const RenderParams& P, Shared& S, Wav
             STAT(kStRecTris, 1);
             if (!e32) STAT(kStRecWide, 1);
         }
-        const bool fast = P.pix_exact && (T.w & 7) == 0 && (T.h & 7) == 0;
+        const bool fast = P.pix_exact;
         // hand int32-form records to the view's record ring (both waves drain it at the end)
         const uint64_t md = __ballot(big && e32);
-        const uint32_t cap = (uint32_t)T.h >> 2;
+        const uint32_t cap = (uint32_t)(T.h + 7 & ~7) >> 2;   // ring records: four framebuffer rows each
         if (md != 0 && cap != 0) {
             const int l0 = __builtin_ctzll(md);
             uint32_t base = 0;
@@ -1338,13 +1355,13 @@ __device__ __forceinline__ void exact_pass(const RenderParams& P, Shared& S, Wav
             if (rj & 256u) {
 #pragma unroll
                 for (int q = 0; q < 9; ++q) uw[q] = readlane(rv[q], l);
-                if (fast) raster_blocks<true, true>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
-                else raster_blocks<true, false>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
+                if (fast) raster_blocks<true, true, kWide>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
+                else raster_blocks<true, false, kWide>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
             } else {
 #pragma unroll
                 for (int q = 0; q < 12; ++q) uw[q] = readlane(rv[q], l);
-                if (fast) raster_blocks<false, true>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
-                else raster_blocks<false, false>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
+                if (fast) raster_blocks<false, true, kWide>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
+                else raster_blocks<false, false, kWide>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
             }
         }
         TACC(kCycRecords, t_rec);
@@ -1358,7 +1375,7 @@ __device__ __forceinline__ void exact_pass(const RenderParams& P, Shared& S, Wav
             const bool sq = aaq && f == 0;   // the whole surface, with the first piece's plane
             const int bx = f == 0 ? X1 : X2, by = f == 0 ? Y1 : Y2;
             const int cx = f == 0 ? X2 : X3, cy = f == 0 ? Y2 : Y3;
-            aa_pieces(P, S, L, fbo, T, sq || (piece && !aaq), sq, sq ? qx[0] : X0, sq ? qy[0] : Y0, sq ? qx[1] : bx,
+            aa_pieces<kWide>(P, S, L, fbo, T, sq || (piece && !aaq), sq, sq ? qx[0] : X0, sq ? qy[0] : Y0, sq ? qx[1] : bx,
                       sq ? qy[1] : by, sq ? qx[2] : cx, sq ? qy[2] : cy, qx[3], qy[3], f ? pa1 : pa0, f ? pb1 : pb0,
                       f ? pc1 : pc0, cls);
         }
@@ -1532,9 +1549,9 @@ __device__ void draw_box_instances(const RenderParams& P, Shared& S, const Tile&
 {
     const int lane = lane_id(), wid = threadIdx.x >> 6;
     WaveLds& L = S.wv[wid];
-    // 128 words of the queue hold the bits of a whole tile, the marks of the packed raster stay in the list
+    // the queue holds the bits of a whole tile, the marks of the packed raster stay in the list
     uint32_t* const bits = L.q;
-    static_assert(kQueue * 32 >= 64 * 64, "coverage bits");
+    static_assert(kQueue * 32 >= kTileWords, "coverage bits");
     const int nw = (T.w * T.h + 31) >> 5;
     for (int k = lane; k < nw; k += 64) bits[k] = 0u;
     uint32_t nclaim = 0;   // pixels this lane's minima gave the agent
@@ -1669,31 +1686,38 @@ __device__ void draw_box_instances(const RenderParams& P, Shared& S, const Tile&
 // culling off are read at run time; otherwise the counter pointer is a
 // constant null and culling constantly on, so every counting site and the
 // unculled paths fold away (and so does the colour code outside modes 2 and 3).
-// kShape (the launcher checks every condition): 0 any view; 1 every tile is
-// 64x64 (the view's width and height are multiples of 64), with exact
-// pixel-centre offsets, 16-byte aligned outputs and depths the fast
+// kShape (the launcher checks every condition): 0 tiles of at most 64x64; 1
+// every tile is 64x64 (the view's width and height are multiples of 64), with
+// exact pixel-centre offsets, 16-byte aligned outputs and depths the fast
 // reciprocal decodes, and no traffic lights; 2 as 1, and the view is one
 // tile.  The tile's size (and with 2 its origin) is then known at compile
 // time, and the paths of other tile shapes, of the IEEE decode and of the
-// lights fold away.
+// lights fold away.  4 as 1 with any tile of at most 64x64: only those paths
+// fold away (8,192 views of 96x54: 271 us against shape 0's 277).  3 any
+// tile, also one wider or taller than 64, whose records and surfaces can have
+// more than 64 blocks: the loops over them cost registers (antialiased 96x54
+// views spill 128 instead of 80 bytes per lane and take 1,011 us instead of
+// 869), so narrower tiles keep the kernels without.
 template <int kMode, bool kDebug, int kShape = 0>
 __global__ __launch_bounds__(kThreads, kWavesPerSimd)
 void render_views_kernel(const RenderParams P_)
 {
     constexpr bool kInst = kMode == 1, kAA = kMode == 2;
-    constexpr bool kTile64 = kShape >= 1;
-    constexpr bool kHasLights = !kTile64;
+    constexpr bool kTile64 = kShape == 1 || kShape == 2, kPlainView = kTile64 || kShape == 4;
+    constexpr bool kHasLights = !kPlainView, kWide = kShape == 3;
     RenderParams P = P_;
     if constexpr (!kDebug) {
         P.stats = nullptr;
         P.cull = 1;
     }
-    if constexpr (kTile64) {
-        P.tile_w = 64; P.tile_h = 64;
+    if constexpr (kPlainView) {
         P.pix_exact = 1;
         P.vec_out = 1;
         P.fast_decode = 1;
         P.L = 0;
+    }
+    if constexpr (kTile64) {
+        P.tile_w = 64; P.tile_h = 64;
     }
     if constexpr (kShape == 2) {
         P.W = 64; P.H = 64;
@@ -1739,7 +1763,7 @@ void render_views_kernel(const RenderParams P_)
         T.w = 64;
         T.h = 64;
     }
-    T.pitch = ((T.w + 31) & ~31) + 4;
+    T.pitch = ((T.w + 7) & ~7) + 4;
     // culling reaches the pixel centres of the tile, and with antialiasing the
     // centres within half a pixel more, where a surface's edge fragments land
     constexpr float tpad = kAA ? 1.0f : 0.5f;
@@ -1755,7 +1779,7 @@ void render_views_kernel(const RenderParams P_)
     {
         // whole padded rows (the pitch is a multiple of 4)
         const u32x4 clr = {kClearKey, kClearKey, kClearKey, kClearKey};
-        const int n4 = T.h * T.pitch;
+        const int n4 = ((T.h + 7) & ~7) * T.pitch;
         for (int p = 4 * tid; p < n4; p += 4 * kThreads) *(u32x4*)&S.fb[p] = clr;
     }
     // per-lane constants of the 8x8 block raster: pixel (lane & 7, lane >> 3)
@@ -1767,13 +1791,13 @@ void render_views_kernel(const RenderParams P_)
     uint32_t* const ebuf = kAA ? (uint32_t*)P.out_depth + v * (int64_t)P.W * P.H + (int64_t)T.y0 * P.W + T.x0 : nullptr;
     if constexpr (kAA) {
         for (int row = wid; row < T.h; row += kViewWaves)
-            if (lane < T.w) ebuf[(int64_t)row * P.W + lane] = 0xFFFFFFFFu;
+            for (int col = lane; col < T.w; col += 64) ebuf[(int64_t)row * P.W + col] = 0xFFFFFFFFu;
     }
     // instance mode: no pixel has an owner yet
     if constexpr (kInst) {
         int32_t* const ibase = P.out_inst + v * (int64_t)P.W * P.H + (int64_t)T.y0 * P.W + T.x0;
         for (int row = wid; row < T.h; row += kViewWaves)
-            if (lane < T.w) ibase[(int64_t)row * P.W + lane] = -1;
+            for (int col = lane; col < T.w; col += 64) ibase[(int64_t)row * P.W + col] = -1;
     }
 
     // world-space frustum planes of the tile: four side planes through the
@@ -2020,7 +2044,7 @@ void render_views_kernel(const RenderParams P_)
             __builtin_amdgcn_wave_barrier();
             STAT1(kStExact, 1);
             TSTART(t_ex);
-            exact_pass<kAA, kHasLights>(P, S, L, T, cam, live, entry, abase_w, lbase_w, pxl, pyl, loff4, ebuf);
+            exact_pass<kAA, kHasLights, kWide>(P, S, L, T, cam, live, entry, abase_w, lbase_w, pxl, pyl, loff4, ebuf);
             TACC(kCycExact, t_ex);
         }
         if (phase == kDone && nq == 0) break;
@@ -2031,8 +2055,8 @@ void render_views_kernel(const RenderParams P_)
     {
         static_assert(kViewWaves == 2, "two done flags");
         if (lane == 0) lds_store_release(&S.ctl[kDone0 + wid], 1u);
-        const uint32_t cap = (uint32_t)T.h >> 2;
-        const bool fast = P.pix_exact && (T.w & 7) == 0 && (T.h & 7) == 0;
+        const uint32_t cap = (uint32_t)(T.h + 7 & ~7) >> 2;   // ring records: four framebuffer rows each
+        const bool fast = P.pix_exact;
         TSTART(t_ring);
         // Every wait below ends: a claimed slot was reserved by a wave that
         // publishes it right after reserving it, and each wave sets its done
@@ -2069,8 +2093,8 @@ void render_views_kernel(const RenderParams P_)
                 const float rpa = __uint_as_float(readfirst(g2.y)), rpb = __uint_as_float(readfirst(g2.z));
                 const float rpc = __uint_as_float(readfirst(g2.w));
                 const uint32_t rb = readfirst(w3[0]), rj = readfirst(w3[1]);
-                if (fast) raster_blocks<true, true>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
-                else raster_blocks<true, false>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
+                if (fast) raster_blocks<true, true, kWide>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
+                else raster_blocks<true, false, kWide>(P, S, T, uw, rpa, rpb, rpc, rb, rj, pxl, pyl, loff4);
                 continue;
             }
             if (fin) break;
@@ -2151,7 +2175,7 @@ void render_views_kernel(const RenderParams P_)
         uint8_t* const rgb = P.out_rgb + v * 3 * view_px;
         if ((reinterpret_cast<uintptr_t>(P.out_rgb) & 3u) == 0 && (P.W % 4) == 0 && (T.w % 4) == 0 && (T.x0 % 4) == 0) {
             // four pixels of a row per thread, one 32-bit store per channel plane
-            // (u / u4 = (u * ceil(2^16 / u4)) >> 16 exactly for u * u4 < 2^16: u < 1024, u4 <= 16)
+            // (u / u4 = (u * ceil(2^16 / u4)) >> 16 exactly for every tile)
             const int u4 = T.w >> 2, n4 = u4 * T.h;
             const uint32_t r4 = (65535u + (uint32_t)u4) / (uint32_t)u4;
             for (int u = tid; u < n4; u += kThreads) {
@@ -2187,14 +2211,17 @@ void render_views_kernel(const RenderParams P_)
         colour_resolve();
         __syncthreads();
     }
-    if (P.vec_out && (P.W % 16) == 0 && (T.w % 16) == 0) {
+    if (P.vec_out && (P.W % 4) == 0 && (T.w % 4) == 0 && (T.x0 % 4) == 0) {
         // tile origin in the view's images; the offsets below stay 32-bit
         uint8_t* const cbase = ocls + ((int64_t)T.y0 * P.W + T.x0);
         float* const dbase = odep + ((int64_t)T.y0 * P.W + T.x0);
-        // u / n = (u * ceil(2^16 / n)) >> 16 exactly for u * n < 2^16 (here u < 1024, n <= 16)
+        // u / n = (u * ceil(2^16 / n)) >> 16 exactly for every tile, as above
+        const int u4 = T.w >> 2, n4 = u4 * T.h;
+        const uint32_t r4 = (65535u + (uint32_t)u4) / (uint32_t)u4;
+        const uint32_t cm = P.out_rgb ? 15u : 255u;   // class byte (R13: the face bits are not part of the class)
+        if ((P.W % 16) == 0 && (T.w % 16) == 0) {
         const int u16 = T.w >> 4, n16 = u16 * T.h;
         const uint32_t r16 = (65535u + (uint32_t)u16) / (uint32_t)u16;
-        const uint32_t cm = P.out_rgb ? 15u : 255u;   // class byte (R13: the face bits are not part of the class)
         for (int u = tid; u < n16; u += kThreads) {
             const int row = (int)(((uint32_t)u * r16) >> 16), c16 = u - row * u16;
             const u32x4* src = (const u32x4*)&S.fb[row * T.pitch + 16 * c16];
@@ -2207,8 +2234,15 @@ void render_views_kernel(const RenderParams P_)
             const u32x4 pk = {wd[0], wd[1], wd[2], wd[3]};
             __builtin_nontemporal_store(pk, (u32x4*)(cbase + (uint32_t)(row * P.W + 16 * c16)));
         }
-        const int u4 = T.w >> 2, n4 = u4 * T.h;
-        const uint32_t r4 = (65535u + (uint32_t)u4) / (uint32_t)u4;
+        } else {
+            // rows that are no whole number of 16-byte stores: four classes per thread
+            for (int u = tid; u < n4; u += kThreads) {
+                const int row = (int)(((uint32_t)u * r4) >> 16), c4 = u - row * u4;
+                const u32x4 kq = *(const u32x4*)&S.fb[row * T.pitch + 4 * c4];
+                const uint32_t pk = (kq.x & cm) | ((kq.y & cm) << 8) | ((kq.z & cm) << 16) | ((kq.w & cm) << 24);
+                __builtin_nontemporal_store(pk, (uint32_t*)(cbase + (uint32_t)(row * P.W + 4 * c4)));
+            }
+        }
         const float inf = __uint_as_float(0x7F800000u);
         auto depth_quad = [&](int u, auto decode) {
             const int row = (int)(((uint32_t)u * r4) >> 16), c4 = u - row * u4;
@@ -2249,10 +2283,24 @@ void render_views_kernel(const RenderParams P_)
 // The most specialised kShape whose assumptions the launch meets.
 static int shape_of(const RenderParams& p)
 {
-    if (!(p.tile_w == 64 && p.tile_h == 64 && p.W % 64 == 0 && p.H % 64 == 0 && p.pix_exact && p.vec_out &&
-          p.fast_decode && p.L == 0))
-        return 0;
+    if (p.tile_w > 64 || p.tile_h > 64) return 3;
+    if (!(p.pix_exact && p.vec_out && p.fast_decode && p.L == 0)) return 0;
+    if (!(p.tile_w == 64 && p.tile_h == 64 && p.W % 64 == 0 && p.H % 64 == 0)) return 4;
     return p.W == 64 && p.H == 64 ? 2 : 1;
+}
+
+// Launch the production kernel of mode kMode for p's shape.
+template <int kMode>
+static void launch_shape(const RenderParams& p, hipStream_t s)
+{
+    const dim3 grid((unsigned)p.num_blocks), block(kThreads);
+    switch (shape_of(p)) {
+    case 1: hipLaunchKernelGGL((render_views_kernel<kMode, false, 1>), grid, block, 0, s, p); break;
+    case 2: hipLaunchKernelGGL((render_views_kernel<kMode, false, 2>), grid, block, 0, s, p); break;
+    case 3: hipLaunchKernelGGL((render_views_kernel<kMode, false, 3>), grid, block, 0, s, p); break;
+    case 4: hipLaunchKernelGGL((render_views_kernel<kMode, false, 4>), grid, block, 0, s, p); break;
+    default: hipLaunchKernelGGL((render_views_kernel<kMode, false, 0>), grid, block, 0, s, p); break;
+    }
 }
 
 #if defined(PICTURA_RENDER_PLAIN)
@@ -2260,29 +2308,15 @@ static int shape_of(const RenderParams& p)
 // holds only the production class/depth kernels.
 hipError_t launch_render_plain(const RenderParams& p, hipStream_t s)
 {
-    const dim3 grid((unsigned)p.num_blocks), block(kThreads);
-    switch (shape_of(p)) {
-    case 2: hipLaunchKernelGGL((render_views_kernel<0, false, 2>), grid, block, 0, s, p); break;
-    case 1: hipLaunchKernelGGL((render_views_kernel<0, false, 1>), grid, block, 0, s, p); break;
-    default: hipLaunchKernelGGL((render_views_kernel<0, false>), grid, block, 0, s, p); break;
-    }
+    launch_shape<0>(p, s);
     return hipGetLastError();
 }
 #elif defined(PICTURA_RENDER_SIDE)
 // Likewise for the production instance (mode 1) and one-sample colour (mode 3) kernels.
 hipError_t launch_render_side(const RenderParams& p, int mode, hipStream_t s)
 {
-    const dim3 grid((unsigned)p.num_blocks), block(kThreads);
-    const int shape = shape_of(p);
-    if (mode == 1) {
-        if (shape == 2) hipLaunchKernelGGL((render_views_kernel<1, false, 2>), grid, block, 0, s, p);
-        else if (shape == 1) hipLaunchKernelGGL((render_views_kernel<1, false, 1>), grid, block, 0, s, p);
-        else hipLaunchKernelGGL((render_views_kernel<1, false>), grid, block, 0, s, p);
-    } else {
-        if (shape == 2) hipLaunchKernelGGL((render_views_kernel<3, false, 2>), grid, block, 0, s, p);
-        else if (shape == 1) hipLaunchKernelGGL((render_views_kernel<3, false, 1>), grid, block, 0, s, p);
-        else hipLaunchKernelGGL((render_views_kernel<3, false>), grid, block, 0, s, p);
-    }
+    if (mode == 1) launch_shape<1>(p, s);
+    else launch_shape<3>(p, s);
     return hipGetLastError();
 }
 #else
@@ -2291,20 +2325,14 @@ hipError_t launch_render(const RenderParams& p, hipStream_t s)
     if (p.num_blocks <= 0) return hipSuccess;
     const dim3 grid((unsigned)p.num_blocks), block(kThreads);
     const int mode = p.out_inst ? 1 : p.out_rgb ? (p.aa ? 2 : 3) : 0;
-    if (p.stats || !p.cull) {
-        if (mode == 1) hipLaunchKernelGGL((render_views_kernel<1, true>), grid, block, 0, s, p);
-        else if (mode == 2) hipLaunchKernelGGL((render_views_kernel<2, true>), grid, block, 0, s, p);
-        else if (mode == 3) hipLaunchKernelGGL((render_views_kernel<3, true>), grid, block, 0, s, p);
-        else hipLaunchKernelGGL((render_views_kernel<0, true>), grid, block, 0, s, p);
-    } else {
-        if (mode == 2) {
-            const int shape = shape_of(p);
-            if (shape == 2) hipLaunchKernelGGL((render_views_kernel<2, false, 2>), grid, block, 0, s, p);
-            else if (shape == 1) hipLaunchKernelGGL((render_views_kernel<2, false, 1>), grid, block, 0, s, p);
-            else hipLaunchKernelGGL((render_views_kernel<2, false>), grid, block, 0, s, p);
-        } else if (mode != 0) return launch_render_side(p, mode, s);
-        else return launch_render_plain(p, s);
-    }
+    if (p.stats || !p.cull) {   // the debug kernels: any tile
+        if (mode == 1) hipLaunchKernelGGL((render_views_kernel<1, true, 3>), grid, block, 0, s, p);
+        else if (mode == 2) hipLaunchKernelGGL((render_views_kernel<2, true, 3>), grid, block, 0, s, p);
+        else if (mode == 3) hipLaunchKernelGGL((render_views_kernel<3, true, 3>), grid, block, 0, s, p);
+        else hipLaunchKernelGGL((render_views_kernel<0, true, 3>), grid, block, 0, s, p);
+    } else if (mode == 2) launch_shape<2>(p, s);
+    else if (mode != 0) return launch_render_side(p, mode, s);
+    else return launch_render_plain(p, s);
     return hipGetLastError();
 }
 
