@@ -366,6 +366,47 @@ pictura_status pictura_selftest_rcp(pictura_ctx ctx, uint32_t lo_bits, uint32_t 
  * Synchronous. */
 pictura_status pictura_selftest_rcp_noalloc(pictura_ctx ctx, uint32_t lo_bits, uint32_t count, uint64_t* mismatches);
 
+/* The policy's image encoder on rendered views (inference).  Per view: one
+ * plane per class and the inverse depth, five 3x3 convolutions with ReLU
+ * (padding 1; 32, 64, 64, 128, 128 channels; strides 2, 2, 1, 2, 1), attention
+ * of the camera's queries over the feature map, mean over the queries,
+ * projection.  Device pointers to contiguous fp32 arrays in PyTorch's layouts:
+ * conv_w[i] [out][in][3][3], queries [cams][16][128], in_proj_w [384][128]
+ * (query, key, value), out_proj_w and proj_w [128][128]; conv_b[1..4] 16-byte
+ * aligned. */
+#define PICTURA_ENCODER_WIDTH 128
+#define PICTURA_ENCODER_HEADS 4
+#define PICTURA_ENCODER_QUERIES 16
+#define PICTURA_ENCODER_MAX_CLASSES 32
+
+typedef struct {
+    int32_t cams;          /* view v is camera v % cams; 1..4096 */
+    int32_t num_classes;   /* 1..PICTURA_ENCODER_MAX_CLASSES; other class IDs have no plane */
+    const float* conv_w[5];
+    const float* conv_b[5];
+    const float* queries;
+    const float* in_proj_w;
+    const float* in_proj_b;
+    const float* out_proj_w;
+    const float* out_proj_b;
+    const float* proj_w;
+    const float* proj_b;
+} pictura_encoder;
+
+/* Bytes of workspace an encode of `views` views of height x width takes (bounded:
+ * larger batches are encoded in several parts).  Reads only cams and num_classes. */
+pictura_status pictura_encoder_workspace(const pictura_encoder* enc, int64_t views, int32_t height, int32_t width,
+                                         uint64_t* bytes);
+
+/* Encode views on `stream` of the current device: cls and depth [views][height]
+ * [width] as rendered, out [views][128] fp32.  workspace: device memory, 256-byte
+ * aligned, in use until the call's work on the stream is done.  EINVAL: a null or
+ * misaligned pointer, sizes out of range, or a workspace too small.  Allocates
+ * nothing and does not synchronise, so it can be captured in a graph. */
+pictura_status pictura_encode_views(const pictura_encoder* enc, const uint8_t* cls, const float* depth, int64_t views,
+                                    int32_t height, int32_t width, void* workspace, uint64_t workspace_bytes,
+                                    float* out, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -6,7 +6,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libpictura.so")
-SOURCES = ["pictura_binner.hip", "pictura_render.hip", "pictura_abi.hip"]
+SOURCES = ["pictura_binner.hip", "pictura_render.hip", "pictura_encoder.hip", "pictura_abi.hip"]
 # (source, object name, extra flags): the render source is compiled three
 # times.  One object holds only the production class/depth kernels, one the
 # production instance and one-sample colour kernels, both scheduled by LLVM's

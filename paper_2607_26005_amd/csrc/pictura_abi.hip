@@ -79,15 +79,6 @@ pictura_status fail(pictura_ctx c, pictura_status st, const char* fmt, ...)
     return st;
 }
 
-Div31 make_div31(uint32_t d)
-{
-    if (d <= 1) return Div31{0u, 0u};
-    uint32_t l = 0;
-    while ((1ull << l) < d) ++l;
-    const uint64_t m = ((1ull << (31 + l)) / d) + 1ull;   // < 2^32 for d >= 2
-    return Div31{(uint32_t)m, l - 1};
-}
-
 // n pixels in `count` even parts, a part's size rounded up to a multiple of
 // `unit` as long as that keeps the count.
 int even_part(int n, int count, int unit)

@@ -59,6 +59,15 @@ struct Div31 {
     uint32_t s;
 };
 
+inline Div31 make_div31(uint32_t d)
+{
+    if (d <= 1) return Div31{0u, 0u};
+    uint32_t l = 0;
+    while ((1ull << l) < d) ++l;
+    const uint64_t m = ((1ull << (31 + l)) / d) + 1ull;   // < 2^32 for d >= 2
+    return Div31{(uint32_t)m, l - 1};
+}
+
 struct RenderParams {
     SceneDev scene;
     // agents (SoA)

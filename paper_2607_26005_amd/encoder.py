@@ -10,8 +10,9 @@ channels, 16 queries per camera and one cross-attention block, a 512-d scene
 embedding).  The paper's views are RGB; here a view is what this renderer writes:
 its class image (one channel per class) and its inverse depth (0 for sky).
 
-This module is PyTorch glue around the renderer (weights are random: the paper's
-trained weights are not available); it adds nothing to the render path.
+The weights are random (the paper's trained weights are not available).  Inference
+on the device runs in the library's kernels (csrc/pictura_encoder.hip); training
+and every other use go through PyTorch's layers.
 """
 from __future__ import annotations
 
@@ -42,9 +43,67 @@ class ViewEncoder(nn.Module):
         inv = torch.reciprocal(depth).unsqueeze(1)   # +inf (sky) -> 0
         return torch.cat([onehot, inv], 1)
 
+    def _native(self, cls: torch.Tensor, depth: torch.Tensor) -> bool:
+        """Whether the library's inference kernels compute this call: plain fp32
+        weights of the shapes built above, rendered views on the device, nothing
+        recorded or transformed on the way (gradients, autocast, tracing, functorch,
+        dispatch modes, hooks)."""
+        if type(cls) is not torch.Tensor or type(depth) is not torch.Tensor or type(self) is not ViewEncoder:
+            return False
+        if not (cls.is_cuda and cls.dtype == torch.uint8 and depth.dtype == torch.float32 and cls.dim() == 3
+                and cls.shape == depth.shape and cls.device == depth.device and cls.is_contiguous()
+                and depth.is_contiguous() and not depth.is_neg()):
+            return False
+        V, H, W = cls.shape
+        if (V == 0 or V % self.cams or not (1 <= H <= 4096 and 1 <= W <= 4096) or not 1 <= self.cams <= 4096
+                or not 1 <= self.num_classes <= 32):
+            return False
+        if (torch.compiler.is_compiling() or torch.jit.is_tracing() or torch.is_autocast_enabled("cuda")
+                or torch._C._len_torch_dispatch_stack() or torch._C._len_torch_function_stack()
+                or torch._C._functorch.peek_interpreter_stack() is not None
+                or torch.autograd.forward_ad._current_level >= 0):
+            return False
+        mods = [self, *self.convs, self.attn, self.attn.out_proj, self.proj, self.convs]
+        gm = nn.modules.module
+        if gm._global_forward_hooks or gm._global_forward_pre_hooks or any(
+                m._forward_hooks or m._forward_pre_hooks for m in mods[1:]) or any(
+                "forward" in m.__dict__ for m in mods) or "planes" in self.__dict__:
+            return False
+        chans, strides = (self.num_classes + 1, 32, 64, 64, 128, 128), (2, 2, 1, 2, 1)
+        a = self.attn
+        if type(self.convs) is not nn.ModuleList or len(self.convs) != 5 or type(a) is not nn.MultiheadAttention \
+                or type(self.proj) is not nn.Linear:
+            return False
+        for i, c in enumerate(self.convs):
+            if (type(c) is not nn.Conv2d or c.weight.shape != (chans[i + 1], chans[i], 3, 3) or c.bias is None
+                    or c.stride != (strides[i],) * 2 or c.padding != (1, 1) or c.dilation != (1, 1) or c.groups != 1
+                    or c.padding_mode != "zeros"):
+                return False
+        if (a.num_heads != 4 or a.embed_dim != 128 or not a.batch_first or not a._qkv_same_embed_dim
+                or a.in_proj_bias is None or a.out_proj.bias is None or a.bias_k is not None or a.add_zero_attn
+                or (a.dropout and a.training) or self.queries.shape != (self.cams, 16, 128)
+                or self.proj.weight.shape != (128, 128) or self.proj.bias is None):
+            return False
+        params = [self.queries, a.in_proj_weight, a.in_proj_bias, a.out_proj.weight, a.out_proj.bias, self.proj.weight,
+                  self.proj.bias, *(p for c in self.convs for p in (c.weight, c.bias))]
+        if any(type(p) not in (nn.Parameter, torch.Tensor) or p.dtype != torch.float32 or p.device != cls.device
+               or not p.is_contiguous() or p.data_ptr() % 16 or p.is_neg() for p in params):
+            return False
+        return not torch.is_grad_enabled() or not (depth.requires_grad or any(p.requires_grad for p in params))
+
     def forward(self, cls: torch.Tensor, depth: torch.Tensor) -> torch.Tensor:
         """cls, depth: [egos * cams, H, W], view v = ego * cams + camera.  Returns the
         [egos, cams * width] scene embedding (mean of each camera's pooled tokens)."""
+        if self._native(cls, depth):
+            from paper_2607_26005_amd import pictura
+            a = self.attn
+            with torch.cuda.device(cls.device):
+                out = torch.empty((cls.shape[0], self.width), dtype=torch.float32, device=cls.device)
+                pictura.pictura_encode_views(self.cams, self.num_classes, [(c.weight, c.bias) for c in self.convs],
+                                             self.queries, (a.in_proj_weight, a.in_proj_bias),
+                                             (a.out_proj.weight, a.out_proj.bias), (self.proj.weight, self.proj.bias),
+                                             cls, depth, out)
+            return out.reshape(cls.shape[0] // self.cams, self.cams * self.width)
         x = self.planes(cls, depth)
         for conv in self.convs:
             x = F.relu(conv(x))

@@ -62,6 +62,13 @@ class _AgentState(ctypes.Structure):
                [(n, ctypes.c_void_p) for n in ("x", "y", "psi", "speed", "cos_h", "sin_h", "length")]
 
 
+class _Encoder(ctypes.Structure):
+    _fields_ = [("cams", ctypes.c_int32), ("num_classes", ctypes.c_int32),
+                ("conv_w", ctypes.c_void_p * 5), ("conv_b", ctypes.c_void_p * 5)] + \
+               [(n, ctypes.c_void_p) for n in ("queries", "in_proj_w", "in_proj_b", "out_proj_w", "out_proj_b",
+                                               "proj_w", "proj_b")]
+
+
 _P = ctypes.c_void_p
 _lib.pictura_create.argtypes = [ctypes.c_int32, ctypes.POINTER(_P)]
 _lib.pictura_create.restype = ctypes.c_int32
@@ -101,12 +108,18 @@ _lib.pictura_store_probe.argtypes = [_P, _P, ctypes.c_uint64, _P]
 _lib.pictura_store_probe.restype = ctypes.c_int32
 _lib.pictura_device_errors.argtypes = [_P, _P, ctypes.c_int32]
 _lib.pictura_device_errors.restype = ctypes.c_int32
+_lib.pictura_encoder_workspace.argtypes = [ctypes.POINTER(_Encoder), ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, _P]
+_lib.pictura_encoder_workspace.restype = ctypes.c_int32
+_lib.pictura_encode_views.argtypes = [ctypes.POINTER(_Encoder), _P, _P, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
+                                      _P, ctypes.c_uint64, _P, _P]
+_lib.pictura_encode_views.restype = ctypes.c_int32
 
 EXPORTED = ["pictura_create", "pictura_destroy", "pictura_last_error", "pictura_scene_upload",
             "pictura_bin_scene", "pictura_render_views", "pictura_agents_step", "pictura_bins_info",
             "pictura_bins_copy", "pictura_set_option", "pictura_stats_copy", "pictura_selftest_rcp",
             "pictura_set_lights", "pictura_render_instances", "pictura_render_rgb", "pictura_render_rgb_aa",
-            "pictura_device_errors", "pictura_selftest_rcp_noalloc", "pictura_store_probe"]
+            "pictura_device_errors", "pictura_selftest_rcp_noalloc", "pictura_store_probe",
+            "pictura_encoder_workspace", "pictura_encode_views"]
 DEVERR_RING_WAIT = 1
 
 STAT_NAMES = ["view_tiles", "cells_in_rect", "cells_prefiltered", "cells_visible", "cand_tris", "boxes_visible",
@@ -377,6 +390,35 @@ def pictura_stats_copy(ctx, reset: bool = True):
     out = np.zeros(len(STAT_NAMES), np.uint64)
     _check(ctx, _lib.pictura_stats_copy(ctx, out.ctypes.data, len(out), int(bool(reset))))
     return dict(zip(STAT_NAMES, (int(x) for x in out)))
+
+
+def pictura_encode_views(cams, num_classes, convs, queries, in_proj, out_proj, proj, cls, depth, out):
+    """Encode rendered views: convs five (weight, bias) pairs, in_proj, out_proj
+    and proj one each, all float32 tensors in PyTorch's layouts on the current
+    device; cls uint8 and depth float32 [V, H, W], out float32 of V * 128
+    elements.  Runs on the current stream in a workspace of the caching
+    allocator."""
+    import torch
+    V, H, W = cls.shape
+    chans = (int(num_classes) + 1, 32, 64, 64, 128, 128)
+    e = _Encoder(int(cams), int(num_classes))
+    for i, (w, b) in enumerate(convs):
+        e.conv_w[i] = _dev(w, f"conv_w[{i}]", "f32", 9 * chans[i] * chans[i + 1])
+        e.conv_b[i] = _dev(b, f"conv_b[{i}]", "f32", chans[i + 1])
+    e.queries = _dev(queries, "queries", "f32", int(cams) * 16 * 128)
+    e.in_proj_w, e.in_proj_b = _dev(in_proj[0], "in_proj_w", "f32", 384 * 128), _dev(in_proj[1], "in_proj_b", "f32", 384)
+    e.out_proj_w, e.out_proj_b = _dev(out_proj[0], "out_proj_w", "f32", 128 * 128), _dev(out_proj[1], "out_proj_b", "f32", 128)
+    e.proj_w, e.proj_b = _dev(proj[0], "proj_w", "f32", 128 * 128), _dev(proj[1], "proj_b", "f32", 128)
+    oc, od = _dev(cls, "cls", "u8", V * H * W), _dev(depth, "depth", "f32", V * H * W)
+    oo = _dev(out, "out", "f32", V * 128)
+    need = ctypes.c_uint64()
+    st = _lib.pictura_encoder_workspace(ctypes.byref(e), V, H, W, ctypes.addressof(need))
+    if st != OK:
+        raise PicturaError(st, "encoder_workspace: sizes out of range")
+    ws = torch.empty(max(int(need.value), 1), dtype=torch.uint8, device=cls.device)
+    st = _lib.pictura_encode_views(ctypes.byref(e), oc, od, V, H, W, ws.data_ptr(), int(need.value), oo, _stream(None))
+    if st != OK:
+        raise PicturaError(st, "encode_views failed")
 
 
 # --- device-resident agents ------------------------------------------------------

@@ -54,3 +54,104 @@ def test_encoder_on_rendered_views_matches_oracle_views():
         assert torch.allclose(got, ref, rtol=1e-4, atol=1e-5), (got - ref).abs().max().item()
     finally:
         r.close_checked()
+
+
+def _views(torch, V, H, W, seed=3):
+    g = torch.Generator().manual_seed(seed)
+    cls = torch.randint(0, 14, (V, H, W), generator=g).to(torch.uint8)   # 11 planes: other IDs have none
+    depth = torch.rand(V, H, W, generator=g) * 100.0 + 0.5
+    depth[cls == 4] = torch.inf
+    return cls.cuda(), depth.cuda()
+
+
+def _exact(torch, enc, cls, depth):
+    # the module's own layers in float64 on the host
+    import copy
+    e = copy.deepcopy(enc).cpu().double()
+    x = e.planes(cls.cpu(), depth.cpu().double()).double()
+    for conv in e.convs:
+        x = torch.relu(conv(x))
+    V = x.shape[0]
+    tok = x.flatten(2).transpose(1, 2).contiguous()
+    pooled, _ = e.attn(e.queries.repeat(V // e.cams, 1, 1), tok, tok, need_weights=False)
+    return e.proj(pooled.mean(1)).reshape(V // e.cams, -1)
+
+
+@pytest.mark.parametrize("V, H, W, cams", [(8, 54, 96, 4), (6, 29, 37, 3), (2, 8, 8, 2), (1, 1, 1, 1), (5, 3, 130, 5),
+                                           (4, 130, 130, 4), (4, 64, 64, 2), (3, 121, 8, 1)])
+def test_native_encoder_matches_float64(V, H, W, cams):
+    # Sizes around the tiles: 256 and 128 output pixels per workgroup, 16
+    # tokens per attention step, and more than 256 tokens (130 x 130: 289).
+    torch = _torch()
+    from paper_2607_26005_amd.encoder import ViewEncoder
+    torch.manual_seed(V * 1000 + H)
+    enc = ViewEncoder(cams=cams).cuda().eval()
+    cls, depth = _views(torch, V, H, W)
+    with torch.no_grad():
+        assert enc._native(cls, depth)
+        got = enc(cls, depth).cpu().double()
+        ref = _exact(torch, enc, cls, depth)
+    # fp32 roundings of the last layers' sums (2^-24 each); the layers before average out
+    assert (got - ref).norm() / ref.norm() < 2.0 ** -22, ((got - ref).norm() / ref.norm()).item()
+
+
+def test_native_encoder_in_parts_and_in_a_graph():
+    torch = _torch()
+    from paper_2607_26005_amd.encoder import ViewEncoder
+    torch.manual_seed(1)
+    enc = ViewEncoder().cuda().eval()
+    cls, depth = _views(torch, 64, 54, 96)
+    with torch.no_grad():
+        small = enc(cls, depth)
+        # more views than one part of the workspace holds
+        big = enc(cls.repeat(160, 1, 1), depth.repeat(160, 1, 1))
+        assert torch.equal(big, small.repeat(160, 1))
+        del big
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            enc(cls, depth)
+        torch.cuda.current_stream().wait_stream(side)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            out = enc(cls, depth)
+        for k in range(3):
+            cls.copy_(cls.roll(1, 0))
+            enc.proj.weight.mul_(1.5)     # weights are read on every replay
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, enc(cls, depth)), k
+
+
+def test_encoder_other_uses_take_the_layers():
+    # gradients, hooks, autocast, other types and layouts are computed by PyTorch's layers as before
+    torch = _torch()
+    from paper_2607_26005_amd.encoder import ViewEncoder
+    torch.manual_seed(2)
+    enc = ViewEncoder().cuda().eval()
+    cls, depth = _views(torch, 4, 20, 24)
+    emb = enc(cls, depth)
+    emb.sum().backward()
+    assert all(p.grad is not None for p in enc.parameters()) and not enc._native(cls, depth)
+    with torch.no_grad():
+        assert enc._native(cls, depth)
+        assert torch.allclose(enc(cls, depth), emb, rtol=1e-5, atol=1e-6)
+        assert not enc._native(cls.long(), depth) and not enc._native(cls, depth.double())
+        assert not enc._native(cls.transpose(1, 2), depth.transpose(1, 2)) and not enc._native(cls.cpu(), depth.cpu())
+        assert not enc._native(cls[:3], depth[:3])
+        with torch.autocast("cuda", torch.bfloat16):
+            assert not enc._native(cls, depth)
+        seen = []
+        hook = enc.convs[2].register_forward_hook(lambda m, i, o: seen.append(o.shape))
+        enc(cls, depth)
+        assert len(seen) == 1
+        hook.remove()
+        for p in enc.parameters():
+            p.requires_grad_(False)
+    assert enc._native(cls, depth)   # frozen weights need no gradients
+    assert not ViewEncoder(width=64).cuda()._native(cls, depth)
+    with torch.no_grad():
+        y = ViewEncoder(width=64).cuda().eval()(cls, depth)
+        assert y.shape == (1, 256)
+        v = torch.func.vmap(lambda c, d: enc.planes(c, d))(cls.unsqueeze(1), depth.unsqueeze(1))
+        assert v.shape == (4, 1, 12, 20, 24)
