@@ -151,13 +151,24 @@ struct BinWork {
     uint32_t* home;              // [P]
     uint32_t* rank;              // [P]
     uint32_t* count;             // [cells + 1] -> exclusive scan -> cell_start
-    uint32_t* aabb_bits;         // [cells][8] order-preserving bits (6 used)
     uint32_t* margin_bits;       // [nw]
     uint32_t* scan_tmp;          // block sums
     int64_t scan_tmp_len;
     float4* primA; float4* primB; float4* primC; float* primD;
     uint32_t* perm;              // [P] the primitive's entry of prims, in cell order
     float4* cell_lo; float4* cell_hi;
+};
+
+// Pairing of an uploaded scene's triangles (owned by the context).
+struct PairWork {
+    const float* verts;          // [T][9]
+    const uint8_t* cls;          // [T]
+    const int64_t* offsets;      // [nw + 1] first triangle of each world
+    int64_t T;
+    int32_t num_worlds;
+    uint2* tiles;                // [pair_tiles_needed(T)]
+    uint32_t* prims;             // [<= T] out, as BinWork::prims
+    int64_t* prim_offsets;       // [nw + 1] out; the last one is the number of primitives
 };
 
 // prims[p]: index of the primitive's first input triangle, with this bit set
@@ -170,6 +181,8 @@ hipError_t launch_render(const RenderParams& p, hipStream_t s);
 // scheduler setting
 hipError_t launch_render_plain(const RenderParams& p, hipStream_t s);
 hipError_t launch_render_side(const RenderParams& p, int mode, hipStream_t s);
+int64_t pair_tiles_needed(int64_t T);
+hipError_t launch_pair(const PairWork& w, hipStream_t s);
 hipError_t launch_bin(const BinWork& w, hipStream_t s);
 hipError_t launch_agents_step(const AgentStepParams& p, hipStream_t s);
 // Pack the num_worlds * A agents of p's SoA arrays into p.apk.
