@@ -1544,23 +1544,23 @@ __device__ __forceinline__ void shade_rgb(const RenderParams& P, uint32_t key, u
 
 // Draw agent `agent`'s box (world index h) alone with the rules R2-R7 and the
 // same arithmetic as the raster: every covered pixel sets its coverage bit in
-// `bits` (bit y * T.w + x), and where its key equals the final key of
-// the view the agent's index enters the pixel of the instance image by an
-// atomic minimum (-1, the fill, is the largest unsigned value), so each pixel
-// goes to the lowest agent whose own frame holds its final key, whichever
-// wave draws first (one triangle of the box with that key there is the same
-// as the box's own minimum being it, as the final key is the minimum over
-// every triangle).  The value the minimum replaced moves the visible counts:
-// an agent that takes a pixel from a higher one also takes its count.  Adds
-// the covered pixels to the agent's footprint.  One wave, one box: lane = face
-// triangle for the set-up; pieces with at most kSmallPx box pixels whose int32
-// edge form fits go through the packed raster together, the others are swept
-// one at a time with exact int64 edge values.  What bounds it is the wave's
-// own chain (about two boxes per view in dense traffic, twelve lanes of set-up
-// each), so the boxes are dealt to all the waves of the tile and the small
-// pieces share their steps: 840 -> 795 us for 32,768 64x64 views of dense
-// traffic, against one wave drawing all boxes in agent order, a triangle at a
-// time (the same views take about 590 us without instances).
+// `bits` (bit y * T.w + x), and where its key equals the final key of the view
+// and no box has claimed the pixel yet, this agent claims it and enters the
+// instance image.  The caller draws the boxes in ascending agent order, so each
+// pixel goes to the lowest agent whose own frame holds its final key (one
+// triangle of the box with that key there is the same as the box's own minimum
+// being it, as the final key is the minimum over every triangle).  The claim
+// bits sit in the framebuffer's padding columns (the four words behind each
+// row, idle once the record ring has drained).  Adds the covered pixels to the
+// agent's footprint and the claimed ones to its visible count.  One wave;
+// lane = face triangle for the set-up; pieces with at most kSmallPx box pixels
+// whose int32 edge form fits go through the packed raster together, the others
+// are swept one at a time with exact int64 edge values.  Dealing the boxes to
+// both waves, owners by global atomic minima whose old values move the counts,
+// was no faster in long launches (32,768 views of dense traffic: 805 us either
+// way; 840 with a triangle at a time instead of the packed raster) and slower
+// in short ones, where every step waits for its atomics (711 views of 118x105:
+// 183 us against 161).
 __device__ void draw_box_instances(const RenderParams& P, Shared& S, const Tile& T, const Cam& cam,
                                    int64_t h, uint32_t agent, int64_t v)
 {
@@ -1571,7 +1571,7 @@ __device__ void draw_box_instances(const RenderParams& P, Shared& S, const Tile&
     static_assert(kQueue * 32 >= kTileWords, "coverage bits");
     const int nw = (T.w * T.h + 31) >> 5;
     for (int k = lane; k < nw; k += 64) bits[k] = 0u;
-    uint32_t nclaim = 0;   // pixels this lane's minima gave the agent
+    uint32_t nclaim = 0;   // pixels this lane claimed
     __builtin_amdgcn_wave_barrier();
     const bool live = lane < 12;
     float tri[9] = {};
@@ -1585,16 +1585,16 @@ __device__ void draw_box_instances(const RenderParams& P, Shared& S, const Tile&
     float pa = 0.0f, pb = 0.0f, pc = 0.0f;
     if (np != 0 && !depth_plane(P, cam, tri, pa, pb, pc)) np = 0;
     const int px0 = 256 * T.x0 + 128, py0 = 256 * T.y0 + 128;
-    uint32_t* const inst = (uint32_t*)P.out_inst + v * (int64_t)P.W * P.H + (int64_t)T.y0 * P.W + T.x0;
+    int32_t* const inst = P.out_inst + v * (int64_t)P.W * P.H + (int64_t)T.y0 * P.W + T.x0;
     // a covered tile pixel (x, y) with key `key`
     auto own = [&](int x, int y, uint32_t key) {
         const int b = y * T.w + x;
         atomicOr(&bits[b >> 5], 1u << (b & 31));
         if (key == S.fb[y * T.pitch + x]) {
-            const uint32_t old = atomicMin(&inst[y * P.W + x], agent);
-            if (old > agent) {
+            const uint32_t c = 1u << (x & 31);
+            if (!(atomicOr(&S.fb[y * T.pitch + T.pitch - 4 + (x >> 5)], c) & c)) {
                 ++nclaim;
-                if (old != 0xFFFFFFFFu) atomicSub(&P.out_counts[2 * (v * P.A + old) + 1], 1u);
+                inst[y * P.W + x] = (int32_t)agent;
             }
         }
     };
@@ -1810,12 +1810,6 @@ void render_views_kernel(const RenderParams P_)
         for (int row = wid; row < T.h; row += kViewWaves)
             for (int col = lane; col < T.w; col += 64) ebuf[(int64_t)row * P.W + col] = 0xFFFFFFFFu;
     }
-    // instance mode: no pixel has an owner yet
-    if constexpr (kInst) {
-        int32_t* const ibase = P.out_inst + v * (int64_t)P.W * P.H + (int64_t)T.y0 * P.W + T.x0;
-        for (int row = wid; row < T.h; row += kViewWaves)
-            for (int col = lane; col < T.w; col += 64) ibase[(int64_t)row * P.W + col] = -1;
-    }
 
     // world-space frustum planes of the tile: four side planes through the
     // camera centre, near and far with margins
@@ -1858,10 +1852,9 @@ void render_views_kernel(const RenderParams P_)
     const int64_t abase_w = (int64_t)w * P.A;
     const int64_t lbase_w = (int64_t)w * P.L;
     if (tid == 0) { STAT(kStTiles, 1); STAT(kStCellsRect, nrect); }
-    // antialiased and instance modes: every wave's fills of the edge buffer (the
-    // instance image) have completed (vmcnt 0) before any wave passes the
-    // barrier and takes minima in it
-    if constexpr (kAA || kInst) __builtin_amdgcn_s_waitcnt(0);
+    // antialiased mode: every wave's fills of the edge buffer have completed
+    // (vmcnt 0) before any wave passes the barrier and adds fragments
+    if constexpr (kAA) __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     TACC(kCycPrologue, t_kernel);
 
@@ -2123,24 +2116,35 @@ void render_views_kernel(const RenderParams P_)
     __syncthreads();
 
     if constexpr (kInst) {
-        // every non-ego box that can reach the tile, dealt to the waves
-        for (int ac = 0; ac * 64 * kViewWaves < P.A; ++ac) {
-            const int ai = (ac * 64 + lane) * kViewWaves + wid;
-            bool vis = ai < P.A && ai != a;
-            if (vis && cull) {
-                const int64_t h = abase_w + ai;
-                const float4 r0 = P.apk[3 * h], r1 = P.apk[3 * h + 1];
-                const float R = 0.5f * (r1.z + r1.w) * 1.0009765625f + 0.0009765625f;
-                vis = aabb_visible(P, T, F, cam, r0.x - R, r0.y - R, r0.z, r0.x + R, r0.y + R, r0.z + r0.w);
-            }
-            uint64_t m = __ballot(vis);
-            while (m) {
-                const int l = __builtin_ctzll(m);
-                m &= m - 1;
-                const uint32_t agent = readlane((uint32_t)ai, l);
-                draw_box_instances(P, S, T, cam, abase_w + agent, agent, v);
+        // claim bits of the tile's pixels
+        for (int r = tid; r < 4 * T.h; r += kThreads) S.fb[(r >> 2) * T.pitch + T.pitch - 4 + (r & 3)] = 0u;
+        __syncthreads();
+        // every non-ego box that can reach the tile, in ascending agent order, by one wave
+        if (wid == 0) {
+            for (int ac = 0; ac * 64 < P.A; ++ac) {
+                const int ai = ac * 64 + lane;
+                bool vis = ai < P.A && ai != a;
+                if (vis && cull) {
+                    const int64_t h = abase_w + ai;
+                    const float4 r0 = P.apk[3 * h], r1 = P.apk[3 * h + 1];
+                    const float R = 0.5f * (r1.z + r1.w) * 1.0009765625f + 0.0009765625f;
+                    vis = aabb_visible(P, T, F, cam, r0.x - R, r0.y - R, r0.z, r0.x + R, r0.y + R, r0.z + r0.w);
+                }
+                uint64_t m = __ballot(vis);
+                while (m) {
+                    const int l = __builtin_ctzll(m);
+                    m &= m - 1;
+                    const uint32_t agent = readlane((uint32_t)ai, l);
+                    draw_box_instances(P, S, T, cam, abase_w + agent, agent, v);
+                }
             }
         }
+        __syncthreads();
+        // pixels no box claimed own nothing (a wave per row)
+        int32_t* const ibase = P.out_inst + v * (int64_t)P.W * P.H + (int64_t)T.y0 * P.W + T.x0;
+        for (int row = wid; row < T.h; row += kViewWaves)
+            for (int col = lane; col < T.w; col += 64)
+                if (!((S.fb[row * T.pitch + T.pitch - 4 + (col >> 5)] >> (col & 31)) & 1u)) ibase[(int64_t)row * P.W + col] = -1;
     }
 
     // ---- R8 resolve + coalesced write-out of the tile ----

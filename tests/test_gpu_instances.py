@@ -187,5 +187,6 @@ def test_instances_ties_between_waves(lib, res, dist, height):
     rig = make_rig(res=res, height=height, mounts=((0.0, 0.0, 0.0, 1.0, 0.0), (0.0, 0.0, 0.0, 0.8, 0.6)))
     wl = sg.Workload("inst-wave-ties", 0, 0, scene, ag, rig, 16.0, 2000.0)
     check(lib, wl, np.arange(wl.num_views), "inst-wave-ties")
+    check(lib, wl, np.arange(wl.num_views), "inst-wave-ties-64", tile=64)
     c = O.render(scene, ag, rig, view_ids=[0], want_instances=True)["counts"][0]
     assert c[1, 1] > 0 and (c[2:6, 1] == 0).all() and (c[2:6, 0] == c[1, 0]).all()
