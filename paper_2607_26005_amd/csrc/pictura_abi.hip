@@ -97,10 +97,15 @@ int even_part(int n, int count, int unit)
 // 16 or of 4 (the vector write-out's units) when the view's is one.  A wider or
 // taller tile is taken only where the framebuffer then holds the view in fewer
 // tiles, as each tile gathers and culls for itself: 100x75 is two tiles of
-// 100x38 instead of four of 52x38 (12,288 colour views: 531 us against 623).  With
+// 100x38 instead of four of 52x38 (12,288 colour views: 531 us against 623), and
+// only in launches of at least three rounds of resident tiles: in shorter ones
+// the larger tiles' tail weighs more (class/depth views of 65x65 in two wide
+// tiles or four: 1,536 views 80 us against 79, 3,072 views 121 against 137;
+// 100x75: 1,536 views 103 against 90, 3,072 views 146 against 158).  With
 // equal counts the 64x64 limit stays: its kernels keep more in registers (128x128
 // views: 855 us in 64x64 tiles, 1,052 in 128x32).
-void choose_tile(int W, int H, int& tw, int& th)
+constexpr int64_t kResidentTiles = 2048;   // eight workgroups on each of 256 CUs
+void choose_tile(int64_t views, int W, int H, int& tw, int& th)
 {
     const int unit = (W % 16) == 0 ? 16 : (W % 4) == 0 ? 4 : 1;
     const int nx0 = (W + 63) / 64, ny0 = (H + 63) / 64;
@@ -114,12 +119,31 @@ void choose_tile(int W, int H, int& tw, int& th)
         int ny = (H + kTileMax - 1) / kTileMax;
         while (nx * ny < best && tile_words(w, (H + ny - 1) / ny) > kTileWords) ++ny;
         const int h = (H + ny - 1) / ny, n = nx * ny;
+        if (views * n < 3 * kResidentTiles) continue;
         if (tile_words(w, h) > kTileWords || n > best || (n == best && (words == 0 || tile_words(w, h) >= words))) continue;
         tw = w;
         th = h;
         best = n;
         words = tile_words(w, h);
     }
+}
+
+// A launch of fewer tiles than the chip holds at once takes as long as its slowest tile, a chain of
+// loads, set-up and raster in two waves.  Its tiles are cut into columns of a
+// multiple of 8 pixels while they all stay resident.  Columns, because they
+// share the work evenly: what a view shows lies in the rows below the horizon.
+// Measured (64x64 class/depth views, whole calls): 8 views 37.8 -> 27.2 us in
+// columns of 8, 128 views 47.7 -> 29.6, 256 views 52.6 -> 37.4 (8), 512 views
+// 54.4 -> 42.5 (16), 1,024 views 57.0 -> 50.3 (32), 512 antialiased views 162 ->
+// 88 (16), 128 views with instances 114 -> 49 (8); 2,048 views in columns of 32
+// would take 78.9 instead of 72.6.
+void narrow_tile(int64_t views, int W, int H, int& tw, int th)
+{
+    const int64_t rows = views * ((H + th - 1) / th);
+    const int64_t cols = kResidentTiles / rows;
+    if (cols < 2) return;
+    const int w = (int)(((W + cols - 1) / cols + 7) / 8 * 8);
+    if (w < tw) tw = w;
 }
 
 pictura_status hip_fail(pictura_ctx c, hipError_t e, const char* what)
@@ -562,7 +586,8 @@ static pictura_status render_setup(pictura_ctx c, const pictura_agents* ag, cons
         tw = c->tile < P.W ? c->tile : P.W;
         th = c->tile < P.H ? c->tile : P.H;
     } else {
-        choose_tile(P.W, P.H, tw, th);
+        choose_tile(V, P.W, P.H, tw, th);
+        narrow_tile(V, P.W, P.H, tw, th);
     }
     P.tile_w = tw; P.tile_h = th;
     P.tiles_x = (P.W + tw - 1) / tw;

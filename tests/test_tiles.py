@@ -1,6 +1,7 @@
 """Views whose tiles are not 64x64: wide tiles (one tile where 64x64 tiles would
 take several), ragged ones and rows that are no whole number of 16-byte stores."""
 import dataclasses
+import functools
 
 import numpy as np
 import pytest
@@ -33,6 +34,11 @@ def test_block_row_split_is_exact():
             assert np.array_equal((b * r) >> 16, b // n), (n, r)
 
 
+@functools.lru_cache(maxsize=None)
+def workload(cfg, worlds):
+    return sg.make_config(cfg, num_worlds=worlds)
+
+
 SIZES = [(100, 75, 0.3), (80, 45, 0.0), (65, 65, 0.0), (96, 96, 0.0), (120, 67, 0.25), (128, 32, 0.0), (128, 33, 0.0),
          (68, 64, 0.0), (30, 120, 0.0), (52, 38, 0.0), (61, 7, 0.0), (4, 4, 0.0), (1, 1, 0.0)]
 
@@ -40,10 +46,19 @@ SIZES = [(100, 75, 0.3), (80, 45, 0.0), (65, 65, 0.0), (96, 96, 0.0), (120, 67, 
 @pytest.mark.gpu
 @pytest.mark.parametrize("w, h, shift", SIZES)
 @pytest.mark.parametrize("mode", ["class", "colour", "antialiased", "instances"])
-def test_tiles_match_the_oracle(mode, w, h, shift):
+@pytest.mark.parametrize("worlds", [1, 12])   # tiles cut into columns; whole and (from 6,144 tiles on) wide ones
+def test_tiles_match_the_oracle(mode, w, h, shift, worlds):
     import torch
     from paper_2607_26005_amd import pictura
-    wl = sg.make_config(7 if h % 2 else 3, num_worlds=1)   # town with lights, or dense traffic
+    wl = workload(7 if h % 2 else 3, worlds)   # town with lights, or dense traffic
+    if worlds > 1 and (w > 64 or h > 64) and w * h < 16000:   # eight cameras: a launch of wide tiles
+        wl = dataclasses.replace(wl, rig=dataclasses.replace(wl.rig, mount=np.concatenate([wl.rig.mount] * 2)))
+        if wl.num_views < 5000:   # (the town has fewer agents: each stands twice in its world)
+            a = wl.agents
+            twice = lambda v: np.repeat(v.reshape(a.num_worlds, -1), 3, 0).reshape(-1)
+            wl = dataclasses.replace(wl, agents=dataclasses.replace(
+                a, agents_per_world=3 * a.agents_per_world, **{f.name: twice(getattr(a, f.name)) for f in dataclasses.fields(a)
+                                                               if isinstance(getattr(a, f.name), np.ndarray)}))
     rig = dataclasses.replace(wl.rig, width=w, height=h, fx=0.6 * w, fy=0.6 * w, cx=w / 2.0 + shift,
                               cy=h / 2.0 - shift)
     print(f"[{mode}] {w}x{h}", flush=True)
