@@ -304,12 +304,29 @@ __device__ __forceinline__ void near_cross(const RenderParams& P, float ix, floa
     y = fmaf(t, oy - iy, iy);
 }
 
-// R9: triangle `face` of agent h's box.
-__device__ __forceinline__ void load_box(const RenderParams& P, int64_t h, int face, float* tri, uint32_t& cls)
+// The kernel's arguments where they lie in memory.  The agents' nine arrays are
+// read through it: their addresses are loaded next to each use (the empty asm
+// keeps the compiler from loading them once and holding 18 scalar registers
+// all the way, which spills others: 12 spilled in the one-tile class/depth
+// kernel).  A kernel that packed the agents for every call before spilled 22 and
+// cost its launch, and an event between streams: 8 views 28.0 -> 22.7 us a
+// call, 8,192 views 181 -> 171, 262,144 views 4,398 -> 4,346.
+typedef const RenderParams __attribute__((address_space(4)))* KernArgs;
+__device__ __forceinline__ KernArgs kernargs()
 {
-    const float4 r0 = P.apk[3 * h], r1 = P.apk[3 * h + 1];
-    const float x = r0.x, y = r0.y, z0 = r0.z, c = r1.x, s = r1.y;
-    const float hl = 0.5f * r1.z, hw = 0.5f * r1.w, ztop = z0 + r0.w;
+    KernArgs k = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return k;
+}
+
+// R9: triangle `face` of the box of agent `a` of the world whose first agent is abase.
+__device__ __forceinline__ void load_box(const RenderParams& P, int64_t abase, uint32_t a, int face, float* tri,
+                                         uint32_t& cls)
+{
+    const KernArgs k = kernargs();
+    const float x = (k->ax + abase)[a], y = (k->ay + abase)[a], z0 = (k->az0 + abase)[a];
+    const float c = (k->ac + abase)[a], s = (k->as + abase)[a];
+    const float hl = 0.5f * (k->al + abase)[a], hw = 0.5f * (k->aw + abase)[a], ztop = z0 + (k->ah + abase)[a];
     // corner indices (bit 0: +L/2, bit 1: +W/2, bit 2: top) of the 12 triangles
     constexpr uint32_t kBoxTris[12] = {0x310, 0x230, 0x754, 0x674, 0x620, 0x460,
                                        0x731, 0x571, 0x510, 0x450, 0x732, 0x672};
@@ -325,7 +342,7 @@ __device__ __forceinline__ void load_box(const RenderParams& P, int64_t h, int f
         tri[3 * q + 1] = y + oy;
         tri[3 * q + 2] = (n & 4) ? ztop : z0;
     }
-    cls = __float_as_uint(P.apk[3 * h + 2].x);
+    cls = (uint32_t)(k->acls + abase)[a];
     // R13: in RGB mode the shading id adds the face (1 bottom, 2 top, 3 back, 4 front, 5 right, 6 left)
     if (P.out_rgb) cls = (cls & 15u) | ((uint32_t)(face >> 1) + 1u) << 4;
 }
@@ -393,7 +410,7 @@ __device__ __forceinline__ bool load_entry(const RenderParams& P, uint32_t e, in
         return false;
     }
     if (e & kBoxFlag) {
-        load_box(P, abase_w + ((e & ~kBoxFlag) >> 4), (int)(e & 15u), tri, cls);
+        load_box(P, abase_w, (e & ~kBoxFlag) >> 4, (int)(e & 15u), tri, cls);
         return false;
     }
     bool pair;
@@ -1467,6 +1484,16 @@ __device__ __forceinline__ bool aabb_visible(const RenderParams& P, const Tile& 
     return box_has_centre(P, T, xmn - sx, xmx + sx, ymn - sy, ymx + sy, mag);
 }
 
+// Can the box of agent `a` (of the world whose first agent is abase) set a key of the tile?
+__device__ __forceinline__ bool box_visible(const RenderParams& P, const Tile& T, const WorldPlanes& F, const Cam& cam,
+                                            int64_t abase, uint32_t a)
+{
+    const KernArgs k = kernargs();
+    const float x = (k->ax + abase)[a], y = (k->ay + abase)[a], z0 = (k->az0 + abase)[a];
+    const float R = 0.5f * ((k->al + abase)[a] + (k->aw + abase)[a]) * 1.0009765625f + 0.0009765625f;
+    return aabb_visible(P, T, F, cam, x - R, y - R, z0, x + R, y + R, z0 + (k->ah + abase)[a]);
+}
+
 __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t nb)
 {
     // Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a
@@ -1542,7 +1569,7 @@ __device__ __forceinline__ void shade_rgb(const RenderParams& P, uint32_t key, u
 // ---------------------------------------------------------------------------
 
 
-// Draw agent `agent`'s box (world index h) alone with the rules R2-R7 and the
+// Draw agent `agent`'s box alone with the rules R2-R7 and the
 // same arithmetic as the raster: every covered pixel sets its coverage bit in
 // `bits` (bit y * T.w + x), and where its key equals the final key of the view
 // and no box has claimed the pixel yet, this agent claims it and enters the
@@ -1561,8 +1588,8 @@ __device__ __forceinline__ void shade_rgb(const RenderParams& P, uint32_t key, u
 // way; 840 with a triangle at a time instead of the packed raster) and slower
 // in short ones, where every step waits for its atomics (711 views of 118x105:
 // 183 us against 161).
-__device__ void draw_box_instances(const RenderParams& P, Shared& S, const Tile& T, const Cam& cam,
-                                   int64_t h, uint32_t agent, int64_t v)
+__device__ __forceinline__ void draw_box_instances(const RenderParams& P, Shared& S, const Tile& T, const Cam& cam,
+                                   int64_t abase, uint32_t agent, int64_t v)
 {
     const int lane = lane_id(), wid = threadIdx.x >> 6;
     WaveLds& L = S.wv[wid];
@@ -1579,7 +1606,7 @@ __device__ void draw_box_instances(const RenderParams& P, Shared& S, const Tile&
     int X0 = 0, Y0 = 0, X1 = 0, Y1 = 0, X2 = 0, Y2 = 0, X3 = 0, Y3 = 0;
     int np = 0;
     if (live) {
-        load_box(P, h, lane, tri, cls);
+        load_box(P, abase, agent, lane, tri, cls);
         np = setup_triangle(P, S, cam, tri, X0, Y0, X1, Y1, X2, Y2, X3, Y3);
     }
     float pa = 0.0f, pb = 0.0f, pc = 0.0f;
@@ -1758,15 +1785,15 @@ void render_views_kernel(const RenderParams P_)
     const int64_t v = (int64_t)v32, g = (int64_t)g32;
     Cam cam;
     {
-        const float4 q0 = P.apk[3 * g], q1 = P.apk[3 * g + 1];
-        const float c = q1.x, s = q1.y;
+        const KernArgs ka = kernargs();
+        const float c = ka->ac[g], s = ka->as[g];
         const float mx = P_.mount[k][0], my = P_.mount[k][1], mz = P_.mount[k][2];
         const float cm = P_.mount[k][3], sm = P_.mount[k][4];
         const float t1 = mx * c, t2 = my * s, t3 = mx * s, t4 = my * c;
         const float ox = t1 - t2, oy = t3 + t4;
-        cam.x = q0.x + ox;
-        cam.y = q0.y + oy;
-        cam.z = q0.z + mz;
+        cam.x = ka->ax[g] + ox;
+        cam.y = ka->ay[g] + oy;
+        cam.z = ka->az0[g] + mz;
         const float u1 = c * cm, u2 = s * sm, u3 = s * cm, u4 = c * sm;
         cam.cc = u1 - u2;
         cam.sc = u3 + u4;
@@ -1936,10 +1963,7 @@ void render_views_kernel(const RenderParams P_)
             if (ai < P.A && ai != a) {
                 vis = true;
                 if (cull) {
-                    const int64_t h = abase_w + ai;
-                    const float4 r0 = P.apk[3 * h], r1 = P.apk[3 * h + 1];
-                    const float R = 0.5f * (r1.z + r1.w) * 1.0009765625f + 0.0009765625f;
-                    vis = aabb_visible(P, T, F, cam, r0.x - R, r0.y - R, r0.z, r0.x + R, r0.y + R, r0.z + r0.w);
+                    vis = box_visible(P, T, F, cam, abase_w, (uint32_t)ai);
                 }
             }
             const uint64_t m = __ballot(vis);
@@ -2035,7 +2059,7 @@ void render_views_kernel(const RenderParams P_)
             const bool boxes = !kHasLights || phase == kBoxes;
             const uint32_t entry = (boxes ? kBoxFlag : kLightFlag) | (ai << 4) | face;
             if (slot < total) {
-                if (boxes) load_box(P, abase_w + ai, (int)face, tri, cls);
+                if (boxes) load_box(P, abase_w, ai, (int)face, tri, cls);
                 else load_light(P, lbase_w + ai, (int)face, tri, cls);
             }
             const bool surv = slot < total && first_pass(P, T, cam, tri, cull);
@@ -2125,17 +2149,14 @@ void render_views_kernel(const RenderParams P_)
                 const int ai = ac * 64 + lane;
                 bool vis = ai < P.A && ai != a;
                 if (vis && cull) {
-                    const int64_t h = abase_w + ai;
-                    const float4 r0 = P.apk[3 * h], r1 = P.apk[3 * h + 1];
-                    const float R = 0.5f * (r1.z + r1.w) * 1.0009765625f + 0.0009765625f;
-                    vis = aabb_visible(P, T, F, cam, r0.x - R, r0.y - R, r0.z, r0.x + R, r0.y + R, r0.z + r0.w);
+                    vis = box_visible(P, T, F, cam, abase_w, (uint32_t)ai);
                 }
                 uint64_t m = __ballot(vis);
                 while (m) {
                     const int l = __builtin_ctzll(m);
                     m &= m - 1;
                     const uint32_t agent = readlane((uint32_t)ai, l);
-                    draw_box_instances(P, S, T, cam, abase_w + agent, agent, v);
+                    draw_box_instances(P, S, T, cam, abase_w, agent, v);
                 }
             }
         }
