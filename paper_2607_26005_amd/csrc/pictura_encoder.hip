@@ -11,12 +11,12 @@
 // matrix cores (2.5 PFLOP/s / 6 against 157 TFLOP/s).  Values are cut once,
 // where they are produced, and stored as [pixel][channels / 32][3][32].
 //
-// Measured on 8,192 views of 96x54: 5.3 ms a call, 15.6 ms through PyTorch's
+// Measured on 8,192 views of 96x54: 4.9 ms a call, 15.6 ms through PyTorch's
 // layers (MIOpen's Winograd convolutions 8.1 ms, the planes, ReLUs and layout
 // changes around them 6 ms, the attention 2 ms).  The error against the same
 // encoder in fp64 is 2.7e-8, 3.1e-8 through the layers.  Kernels: first
-// convolution 0.73 ms (2.0 GB written), then 0.98, 1.48, 0.71 and 1.19 ms (0.62,
-// 0.82, 0.85 and 1.03 PFLOP/s of bf16 products; a large bf16 matrix product
+// convolution 0.73 ms (2.0 GB written), then 0.99, 1.14, 0.71 and 1.06 ms (0.61,
+// 1.07, 0.85 and 1.15 PFLOP/s of bf16 products; a large bf16 matrix product
 // reaches 1.15 on this card), attention 0.40 ms.
 #include <cmath>
 
@@ -265,6 +265,86 @@ __global__ __launch_bounds__(256) void enc_conv1_kernel(const uint8_t* __restric
 // 16 bytes a lane for 24 products of 32 cycles).
 constexpr int kRowBytes = 80;
 
+// The products of a staged chunk: weight rows of this lane (parts kCout rows
+// apart), and its two pixel rows (parts kARows rows apart).
+template <int kCout, int kARows>
+__device__ __forceinline__ void enc_products(const uint8_t* wrow, const uint8_t* prow0, const uint8_t* prow1, int lane,
+                                             f32x16 (&acc)[2][2])
+{
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        const int ko = ks * 32 + (lane >> 5) * 16;
+        bf16x8 wf[2][3], pf[2][3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            wf[0][q] = *(const bf16x8*)(wrow + q * kCout * kRowBytes + ko);
+            wf[1][q] = *(const bf16x8*)(wrow + (q * kCout + 32) * kRowBytes + ko);
+            pf[0][q] = *(const bf16x8*)(prow0 + q * kARows * kRowBytes + ko);
+            pf[1][q] = *(const bf16x8*)(prow1 + q * kARows * kRowBytes + ko);
+        }
+        // the smallest products first
+        constexpr int kW[6] = {2, 0, 1, 1, 0, 0}, kP[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int t = 0; t < 6; ++t)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[i][kW[t]], pf[j][kP[t]], acc[i][j], 0, 0, 0);
+    }
+}
+
+template <int kCout, int MT, bool kLast>
+__device__ __forceinline__ void enc_store(f32x16 (&acc)[2][2], uint8_t* sA, const float* __restrict__ bias, int64_t p0,
+                                          int64_t pixels, int wm, int wn, void* __restrict__ out)
+{
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    // bias, ReLU (a NaN stays one); lane: pixel column lane & 31, channels 8 g + 4 (lane >> 5) .. + 3 of group g.
+    // The parts of 32 channels go through the wave's share of LDS, so that the stores are whole rows of 192 bytes.
+    constexpr int kOutPitch = 208;
+    if constexpr (!kLast) __syncthreads();
+    uint8_t* const so = sA + wid * 64 * kOutPitch;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int c = g * 8 + (lane >> 5) * 4, n = wn * 64 + i * 32 + c;
+                const f32x4 b = *(const f32x4*)(bias + n);
+                f32x4 x;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float s = acc[i][j][g * 4 + r] + b[r];
+                    x[r] = s < 0.0f ? 0.0f : s;
+                }
+                if constexpr (kLast) {
+                    const int64_t px = p0 + wm * 64 + j * 32 + (lane & 31);
+                    if (px < pixels) *(f32x4*)((float*)out + px * kCout + n) = x;
+                } else {
+                    uint32_t ph[4], pm[4], pl[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) split3(x[r], ph[r], pm[r], pl[r]);
+                    uint8_t* o = so + (j * 32 + (lane & 31)) * kOutPitch + c * 2;
+                    *(u32x2*)o = pack4(ph);
+                    *(u32x2*)(o + 64) = pack4(pm);
+                    *(u32x2*)(o + 128) = pack4(pl);
+                }
+            }
+        if constexpr (!kLast) {
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int s = 0; s < 12; ++s) {
+                const int q = s * 64 + lane, row = q / 12, at = q - row * 12;
+                const int64_t px = p0 + wm * 64 + row;
+                const u32x4 d = *(const u32x4*)(so + row * kOutPitch + at * 16);
+                if (px < pixels) *((u32x4*)out + (px * (kCout / 32) + wn * 2 + i) * 12 + at) = d;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+}
+
 template <int kCin, int kCout, int kStride, int MT, bool kLast>
 __global__ __launch_bounds__(256, 2) void enc_conv_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ wk,
                                                           const float* __restrict__ bias, int hi, int wi, int h, int w,
@@ -337,73 +417,119 @@ __global__ __launch_bounds__(256, 2) void enc_conv_kernel(const uint16_t* __rest
         }
         __syncthreads();
         if (ch + 1 < kChunks) fetch(ch + 1);
+        enc_products<kCout, MT>(sB + (wn * 64 + (lane & 31)) * kRowBytes, sA + (wm * 64 + (lane & 31)) * kRowBytes,
+                                sA + (wm * 64 + 32 + (lane & 31)) * kRowBytes, lane, acc);
+    }
+    enc_store<kCout, MT, kLast>(acc, sA, bias, p0, pixels, wm, wn, out);
+}
+
+// The same with stride 1, where the three taps of a kernel row read the same
+// pixels one apart: a row of MT + 2 consecutive pixels is staged once for the
+// three (their weights one tap at a time), and a lane whose pixel has no
+// neighbour there reads a row of zeros.  Staging is what holds the general
+// kernel back: with 0.47 and 0.67 of its bytes the 64- and 128-channel
+// convolutions of 8,192 views take 1.14 instead of 1.48 ms and 1.06 instead of
+// 1.19.
+template <int kCin, int kCout, int MT, bool kLast>
+__global__ __launch_bounds__(256, 2) void enc_conv_s1_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ wk,
+                                                             const float* __restrict__ bias, int h, int w, int64_t pixels,
+                                                             void* __restrict__ out)
+{
+    constexpr int kWavesN = kCout / 64, kWavesM = 4 / kWavesN;
+    static_assert(MT == 64 * kWavesM, "four waves of 64 x 64");
+    constexpr int kSteps = kCin / kKC;
+    constexpr int kRows = MT / 64, kARows = MT + 3;   // the last row is zero
+    constexpr int kBLoads = kCout * 3 * 4 / 256;
+    constexpr int kABytes = 3 * kARows * kRowBytes, kLdsBytes = kABytes + 3 * kCout * kRowBytes;
+    __shared__ __align__(16) uint8_t sA[kLdsBytes];
+    static_assert(kLast || 4 * 64 * 208 <= kLdsBytes, "output rows of four waves");
+    uint8_t* const sB = sA + kABytes;
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int wm = wid % kWavesM, wn = wid / kWavesM;
+    const int64_t p0 = (int64_t)blockIdx.x * MT;
+    const int piece = tid & 3, hw = h * w;
+    if (tid < 3 * kRowBytes / 16)
+        *(u32x4*)&sA[((tid / 5) * kARows + kARows - 1) * kRowBytes + (tid % 5) * 16] = u32x4{0u, 0u, 0u, 0u};
+    // this lane's two pixels: the taps that have a neighbour, a bit each
+    uint32_t taps[2];
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const int ko = ks * 32 + (lane >> 5) * 16;
-            bf16x8 wf[2][3], pf[2][3];
+    for (int j = 0; j < 2; ++j) {
+        const int64_t px = p0 + wm * 64 + j * 32 + (lane & 31);
+        taps[j] = 0;
+        if (px < pixels) {
+            const int r = (int)(px % hw), y = r / w, x = r - y * w;
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    wf[i][q] = *(const bf16x8*)&sB[(q * kCout + wn * 64 + i * 32 + (lane & 31)) * kRowBytes + ko];
-                    pf[i][q] = *(const bf16x8*)&sA[(q * MT + wm * 64 + i * 32 + (lane & 31)) * kRowBytes + ko];
-                }
-            // the smallest products first
-            constexpr int kW[6] = {2, 0, 1, 1, 0, 0}, kP[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-            for (int t = 0; t < 6; ++t)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[i][kW[t]], pf[j][kP[t]], acc[i][j], 0, 0, 0);
+            for (int t = 0; t < kTaps; ++t)
+                if (y + t / 3 - 1 >= 0 && y + t / 3 - 1 < h && x + t % 3 - 1 >= 0 && x + t % 3 - 1 < w) taps[j] |= 1u << t;
         }
     }
-    // bias, ReLU (a NaN stays one); lane: pixel column lane & 31, channels 8 g + 4 (lane >> 5) .. + 3 of group g.
-    // The parts of 32 channels go through the wave's share of LDS, so that the stores are whole rows of 192 bytes.
-    constexpr int kOutPitch = 208;
-    static_assert(kLast || 4 * 64 * kOutPitch <= kLdsBytes, "output rows of four waves");
-    if constexpr (!kLast) __syncthreads();
-    uint8_t* const so = sA + wid * 64 * kOutPitch;
+    u32x4 ra[3 * kRows], rx[3], rb[kBLoads];
+    // pixel rows of kernel row dy and chunk c; row r is pixel p0 - 1 + r + (dy - 1) w
+    // (one outside the buffer is loaded from its end: no lane reads it)
+    auto fetch_a = [&](int dy, int c) {
+        const u32x4* a = (const u32x4*)in + c * 12 + piece;
+        const int64_t q0 = p0 - 1 + (int64_t)(dy - 1) * w + (tid >> 2);
+        auto at = [&](int64_t q) { return a + (q < 0 ? 0 : q < pixels ? q : pixels - 1) * (12 * kSteps); };
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < kRows; ++i) {
+            const u32x4* p = at(q0 + i * 64);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) ra[i * 3 + q] = p[4 * q];
+        }
+        if (tid < 8) {
+            const u32x4* p = at(q0 + MT);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) rx[q] = p[4 * q];
+        }
+    };
+    auto fetch_b = [&](int tap, int c) {
+        const u32x4* b = (const u32x4*)(wk + (int64_t)(tap * kSteps + c) * 3 * kCout * kKC);
+#pragma unroll
+        for (int s = 0; s < kBLoads; ++s) rb[s] = b[tid + 256 * s];
+    };
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int c = g * 8 + (lane >> 5) * 4, n = wn * 64 + i * 32 + c;
-                const f32x4 b = *(const f32x4*)(bias + n);
-                f32x4 x;
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    fetch_a(0, 0);
+    fetch_b(0, 0);
+#pragma unroll 1
+    for (int g = 0; g < 3 * kSteps; ++g) {   // kernel row and chunk
+        const int dy = g / kSteps, c = g - dy * kSteps;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float s = acc[i][j][g * 4 + r] + b[r];
-                    x[r] = s < 0.0f ? 0.0f : s;
-                }
-                if constexpr (kLast) {
-                    const int64_t px = p0 + wm * 64 + j * 32 + (lane & 31);
-                    if (px < pixels) *(f32x4*)((float*)out + px * kCout + n) = x;
-                } else {
-                    uint32_t ph[4], pm[4], pl[4];
+        for (int dx = 0; dx < 3; ++dx) {
+            __syncthreads();   // the last tap's reads are done
+            if (dx == 0) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) split3(x[r], ph[r], pm[r], pl[r]);
-                    uint8_t* o = so + (j * 32 + (lane & 31)) * kOutPitch + c * 2;
-                    *(u32x2*)o = pack4(ph);
-                    *(u32x2*)(o + 64) = pack4(pm);
-                    *(u32x2*)(o + 128) = pack4(pl);
+                for (int i = 0; i < kRows; ++i)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        *(u32x4*)&sA[(q * kARows + i * 64 + (tid >> 2)) * kRowBytes + piece * 16] = ra[i * 3 + q];
+                if (tid < 8) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        *(u32x4*)&sA[(q * kARows + MT + (tid >> 2)) * kRowBytes + piece * 16] = rx[q];
                 }
             }
-        if constexpr (!kLast) {
-            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int s = 0; s < 12; ++s) {
-                const int q = s * 64 + lane, row = q / 12, at = q - row * 12;
-                const int64_t px = p0 + wm * 64 + row;
-                const u32x4 d = *(const u32x4*)(so + row * kOutPitch + at * 16);
-                if (px < pixels) *((u32x4*)out + (px * (kCout / 32) + wn * 2 + i) * 12 + at) = d;
+            for (int s = 0; s < kBLoads; ++s) {
+                const int p = tid + 256 * s;
+                *(u32x4*)&sB[(p >> 2) * kRowBytes + (p & 3) * 16] = rb[s];
             }
-            __builtin_amdgcn_wave_barrier();
+            __syncthreads();
+            if (dx < 2) fetch_b(dy * 3 + dx + 1, c);
+            else if (g + 1 < 3 * kSteps) fetch_b((g + 1) / kSteps * 3, (g + 1) % kSteps);
+            if (dx == 0 && g + 1 < 3 * kSteps) fetch_a((g + 1) / kSteps, (g + 1) % kSteps);
+            const int t = dy * 3 + dx, r0 = wm * 64 + (lane & 31) + dx;
+            const int a0 = (taps[0] >> t) & 1u ? r0 : kARows - 1, a1 = (taps[1] >> t) & 1u ? r0 + 32 : kARows - 1;
+            enc_products<kCout, kARows>(sB + (wn * 64 + (lane & 31)) * kRowBytes, sA + a0 * kRowBytes, sA + a1 * kRowBytes,
+                                        lane, acc);
         }
     }
+    enc_store<kCout, MT, kLast>(acc, sA, bias, p0, pixels, wm, wn, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -689,12 +815,12 @@ pictura_status pictura_encode_views(const pictura_encoder* e, const uint8_t* cls
                            make_div31((uint32_t)(p.h[0] * p.w[0])), make_div31((uint32_t)p.w[0]), (int)px[0], A);
         hipLaunchKernelGGL((enc_conv_kernel<kC1, kC2, 2, 256, false>), blocks(px[1], 256), dim3(256), 0, s, A, W.wk[0],
                            W.cb[1], p.h[0], p.w[0], p.h[1], p.w[1], px[1], (void*)B);
-        hipLaunchKernelGGL((enc_conv_kernel<kC2, kC3, 1, 256, false>), blocks(px[2], 256), dim3(256), 0, s, B, W.wk[1],
-                           W.cb[2], p.h[1], p.w[1], p.h[2], p.w[2], px[2], (void*)A);
+        hipLaunchKernelGGL((enc_conv_s1_kernel<kC2, kC3, 256, false>), blocks(px[2], 256), dim3(256), 0, s, B, W.wk[1],
+                           W.cb[2], p.h[2], p.w[2], px[2], (void*)A);
         hipLaunchKernelGGL((enc_conv_kernel<kC3, kC4, 2, 128, false>), blocks(px[3], 128), dim3(256), 0, s, A, W.wk[2],
                            W.cb[3], p.h[2], p.w[2], p.h[3], p.w[3], px[3], (void*)B);
-        hipLaunchKernelGGL((enc_conv_kernel<kC4, kC5, 1, 128, true>), blocks(px[4], 128), dim3(256), 0, s, B, W.wk[3],
-                           W.cb[4], p.h[3], p.w[3], p.h[4], p.w[4], px[4], (void*)A);
+        hipLaunchKernelGGL((enc_conv_s1_kernel<kC4, kC5, 128, true>), blocks(px[4], 128), dim3(256), 0, s, B, W.wk[3],
+                           W.cb[4], p.h[4], p.w[4], px[4], (void*)A);
         const int tokens = p.h[4] * p.w[4];
         if (tokens <= 256)
             hipLaunchKernelGGL(enc_attn_kernel<true>, dim3((unsigned)nv), dim3(256),
