@@ -4,10 +4,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <mutex>
 #include <string>
-#include <system_error>
-#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -232,89 +229,6 @@ int64_t count_prims(int nw, const int64_t* offs, const float* verts, const uint8
     return n;
 }
 
-// Pinned staging for host-to-device copies, shared by the contexts of the
-// process and freed with the last one: kStageThreads threads copy a piece each
-// into pinned slots of their own while the last one's DMA runs.  The runtime's
-// path for pageable memory copies with one thread; an upload of 64 worlds of 45 K
-// triangles (105 MB) takes 3.7 ms instead of 11.0 with this, the pairing on the
-// device and the last scene's arrays kept.  Copies of up to 4 MB go the
-// runtime's way: starting threads costs more than it gives there.
-constexpr int kStageThreads = 8, kStageSlots = 2;
-constexpr size_t kStageBytes = 1 << 20;   // of a slot
-struct Stage {
-    std::mutex mu;        // held during a copy: one upload stages at a time
-    int refs = 0;
-    uint8_t* buf = nullptr;
-};
-Stage g_stage;
-
-void stage_ref(int d)
-{
-    std::lock_guard<std::mutex> lock(g_stage.mu);
-    g_stage.refs += d;
-    if (g_stage.refs == 0 && g_stage.buf) {
-        (void)hipHostFree(g_stage.buf);
-        g_stage.buf = nullptr;
-    }
-}
-
-// Copy n bytes of pageable host memory to dst on stream st; on return the host
-// memory may be reused.
-hipError_t upload_bytes(int device, void* dst, const void* src, size_t n, hipStream_t st)
-{
-    constexpr size_t kDirect = 4 * kStageBytes;
-    if (n <= kDirect) return n ? hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, st) : hipSuccess;
-    std::unique_lock<std::mutex> lock(g_stage.mu);
-    if (!g_stage.buf &&
-        hipHostMalloc((void**)&g_stage.buf, kStageThreads * kStageSlots * kStageBytes, hipHostMallocPortable) != hipSuccess) {
-        (void)hipGetLastError();
-        g_stage.buf = nullptr;
-        lock.unlock();
-        return hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, st);
-    }
-    const size_t pieces = (n + kStageBytes - 1) / kStageBytes;
-    hipError_t err[kStageThreads];
-    auto work = [&](int k) {
-        hipEvent_t ev[kStageSlots] = {};
-        hipError_t e = hipSetDevice(device);
-        for (int q = 0; q < kStageSlots && e == hipSuccess; ++q) e = hipEventCreateWithFlags(&ev[q], hipEventDisableTiming);
-        int used = 0;
-        for (size_t i = (size_t)k; i < pieces && e == hipSuccess; i += kStageThreads, ++used) {
-            const int q = used % kStageSlots;
-            uint8_t* slot = g_stage.buf + (size_t)(k * kStageSlots + q) * kStageBytes;
-            if (used >= kStageSlots && (e = hipEventSynchronize(ev[q])) != hipSuccess) break;
-            const size_t at = i * kStageBytes, m = n - at < kStageBytes ? n - at : kStageBytes;
-            std::memcpy(slot, (const uint8_t*)src + at, m);
-            if ((e = hipMemcpyAsync((uint8_t*)dst + at, slot, m, hipMemcpyHostToDevice, st)) == hipSuccess)
-                e = hipEventRecord(ev[q], st);
-        }
-        // the slots are free again when the thread's copies are done
-        for (int q = 0; q < kStageSlots; ++q) {
-            if (!ev[q]) continue;
-            if (q < used) {
-                const hipError_t w = hipEventSynchronize(ev[q]);
-                if (e == hipSuccess) e = w;
-            }
-            (void)hipEventDestroy(ev[q]);
-        }
-        err[k] = e;
-    };
-    std::thread th[kStageThreads];
-    for (int k = 1; k < kStageThreads; ++k) {
-        try {
-            th[k] = std::thread(work, k);
-        } catch (const std::system_error&) {
-            work(k);   // no thread to be had: this one's pieces in line
-        }
-    }
-    work(0);
-    for (int k = 1; k < kStageThreads; ++k)
-        if (th[k].joinable()) th[k].join();
-    for (int k = 0; k < kStageThreads; ++k)
-        if (err[k] != hipSuccess) return err[k];
-    return hipSuccess;
-}
-
 uint32_t f2u(float f) { uint32_t u; std::memcpy(&u, &f, 4); return u; }
 float u2f(uint32_t u) { float f; std::memcpy(&f, &u, 4); return f; }
 
@@ -351,7 +265,6 @@ pictura_status pictura_create(int32_t device, pictura_ctx* out)
             return PICTURA_EDEVICE;
         }
     }
-    stage_ref(1);
     *out = c;
     return PICTURA_OK;
 }
@@ -364,7 +277,6 @@ void pictura_destroy(pictura_ctx c)
         (void)hipDeviceSynchronize();
         free_scene(c);
         dfree(c->dev_err);
-        stage_ref(-1);
     }
     delete c;
 }
@@ -421,9 +333,14 @@ pictura_status pictura_scene_upload(pictura_ctx c, const pictura_scene* s, void*
     }
     int64_t P = 0;
     PairWork W{c->verts, c->cls, c->offsets_d, T, nw, c->pair_tiles, c->prims, c->prim_offsets_d};
-    if ((e = upload_bytes(c->device, c->verts, s->verts, (size_t)T * 9 * sizeof(float), st)) != hipSuccess ||
-        (e = upload_bytes(c->device, c->cls, s->cls, (size_t)T, st)) != hipSuccess ||
-        (e = upload_bytes(c->device, c->offsets_d, s->tri_offsets, (size_t)(nw + 1) * sizeof(int64_t), st)) != hipSuccess) {
+    // (pageable memory: the runtime's copies run at the link's rate, 28 GB/s here;
+    // eight threads copying through pinned slots were no faster)
+    auto copy = [&](void* dst, const void* src, size_t n) {
+        return n ? hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, st) : hipSuccess;
+    };
+    if ((e = copy(c->verts, s->verts, (size_t)T * 9 * sizeof(float))) != hipSuccess ||
+        (e = copy(c->cls, s->cls, (size_t)T)) != hipSuccess ||
+        (e = copy(c->offsets_d, s->tri_offsets, (size_t)(nw + 1) * sizeof(int64_t))) != hipSuccess) {
         free_scene(c);
         return hip_fail(c, e, "scene_upload copy");
     }
