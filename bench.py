@@ -43,8 +43,8 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E peak
 # `traffic` is reported as null.
 TRAFFIC = {
     "config": 4,
-    "sources_sha256": "5ea88b326a9df7bc350c6b5ef16ea98b3c6baff4c1e50137f15d573cfa7593ec",
-    "fetch_bytes": 1.1546e9,
+    "sources_sha256": "50e77c2cfa033018ffc84d15da5a3418f4bbe429dd74eaea591e8e0fbc04cb76",
+    "fetch_bytes": 1.1530e9,
     "write_bytes": 5368709120,
 }
 TRAFFIC_SOURCES = ["paper_2607_26005_amd/csrc/pictura_render.hip",
@@ -319,7 +319,7 @@ def main():
             "algorithmic_bytes_per_launch": out_bytes,
             "traffic": traffic,
             "traffic_source": ("rocprofv3 FETCH_SIZE + WRITE_SIZE per launch, copy-calibrated, profiled on these kernel "
-                               "sources (profiles/render_views_kernel_throughput_headline_64x64.md)"
+                               "sources (profiles/kernels_current.md)"
                                if traffic is not None else None),
             "measured_store_gbs": store_gbs,
             "frac_of_measured_store": achieved / store_gbs,
