@@ -43,7 +43,7 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E peak
 # `traffic` is reported as null.
 TRAFFIC = {
     "config": 4,
-    "sources_sha256": "50e77c2cfa033018ffc84d15da5a3418f4bbe429dd74eaea591e8e0fbc04cb76",
+    "sources_sha256": "b6ab9f13c1bbdadc692e3441d2867c791502438484a0e89202ecf2936475db84",
     "fetch_bytes": 1.1530e9,
     "write_bytes": 5368709120,
 }

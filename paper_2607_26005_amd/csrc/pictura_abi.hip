@@ -58,6 +58,11 @@ struct pictura_ctx_s {
     // traffic lights (caller-owned device arrays; lights.lights_per_world == 0: none)
     pictura_lights lights{};
     uint32_t* dev_err = nullptr;   // device error word (pictura_device_errors), allocated by pictura_create
+    // a render call on another stream than the last one is ordered after that
+    // call's kernels: each call records the event behind its own
+    hipEvent_t order_event = nullptr;
+    hipStream_t order_stream = nullptr;
+    bool order_used = false;
 };
 
 namespace {
@@ -277,6 +282,7 @@ void pictura_destroy(pictura_ctx c)
         (void)hipDeviceSynchronize();
         free_scene(c);
         dfree(c->dev_err);
+        if (c->order_event) (void)hipEventDestroy(c->order_event);
     }
     delete c;
 }
@@ -531,6 +537,24 @@ static pictura_status render_setup(pictura_ctx c, const pictura_agents* ag, cons
     return PICTURA_OK;
 }
 
+// Launch a render set up by render_setup on stream s, behind the context's
+// last render call if that was on another stream (a caller may step or free
+// the agents on s afterwards, and both calls read them in place).
+static hipError_t render_launch(pictura_ctx c, const RenderParams& P, hipStream_t s)
+{
+    hipError_t e = hipSuccess;
+    if (!c->order_event && (e = hipEventCreateWithFlags(&c->order_event, hipEventDisableTiming)) != hipSuccess) {
+        c->order_event = nullptr;
+        return e;
+    }
+    if (c->order_used && c->order_stream != s && (e = hipStreamWaitEvent(s, c->order_event, 0)) != hipSuccess) return e;
+    if ((e = launch_render(P, s)) != hipSuccess) return e;
+    if ((e = hipEventRecord(c->order_event, s)) != hipSuccess) return e;
+    c->order_stream = s;
+    c->order_used = true;
+    return hipSuccess;
+}
+
 pictura_status pictura_render_views(pictura_ctx c, const pictura_agents* ag, const pictura_rig* rig,
                                     uint8_t* out_cls, float* out_depth, void* stream)
 {
@@ -541,7 +565,7 @@ pictura_status pictura_render_views(pictura_ctx c, const pictura_agents* ag, con
     bool empty = false;
     const pictura_status st = render_setup(c, ag, rig, out_cls, out_depth, P, &empty);
     if (st != PICTURA_OK || empty) return st;
-    hipError_t e = launch_render(P, (hipStream_t)stream);
+    hipError_t e = render_launch(c, P, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "render_views launch");
     return PICTURA_OK;
 }
@@ -561,7 +585,7 @@ static pictura_status render_rgb(pictura_ctx c, const pictura_agents* ag, const 
     P.out_rgb = out_rgb;
     P.rfar = 1.0f / P.farp;
     P.aa = aa ? 1 : 0;
-    hipError_t e = launch_render(P, (hipStream_t)stream);
+    hipError_t e = render_launch(c, P, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "render_rgb launch");
     return PICTURA_OK;
 }
@@ -594,7 +618,7 @@ pictura_status pictura_render_instances(pictura_ctx c, const pictura_agents* ag,
     P.out_counts = out_counts;
     hipError_t e = launch_fill_u32(out_counts, (size_t)P.num_views * (size_t)P.A * 2u, 0u, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "render_instances clear");
-    e = launch_render(P, (hipStream_t)stream);
+    e = render_launch(c, P, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "render_instances launch");
     return PICTURA_OK;
 }

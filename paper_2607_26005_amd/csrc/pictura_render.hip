@@ -309,8 +309,8 @@ __device__ __forceinline__ void near_cross(const RenderParams& P, float ix, floa
 // keeps the compiler from loading them once and holding 18 scalar registers
 // all the way, which spills others: 12 spilled in the one-tile class/depth
 // kernel).  A kernel that packed the agents for every call before spilled 22 and
-// cost its launch, and an event between streams: 8 views 28.0 -> 22.7 us a
-// call, 8,192 views 181 -> 171, 262,144 views 4,398 -> 4,346.
+// cost its launch: 8,192 views 181 -> 171 us a call, 262,144 views 4,398 ->
+// 4,346.
 typedef const RenderParams __attribute__((address_space(4)))* KernArgs;
 __device__ __forceinline__ KernArgs kernargs()
 {
