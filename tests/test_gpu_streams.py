@@ -1,7 +1,5 @@
-"""Render calls of one context on two streams.  Every render call first packs
-its agents into the context's one device buffer and then runs its kernels, so
-a call on another stream than the previous one must not pack before that
-call's kernels are done; the library orders it after them with an event.
+"""Render calls of one context on two streams.  A call on another stream than
+the previous one is ordered after that call's kernels with an event.
 Different agent sets rendered back to back on two streams must give the images
 each set gives alone."""
 import numpy as np
