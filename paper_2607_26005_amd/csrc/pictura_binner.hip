@@ -300,9 +300,11 @@ __device__ __forceinline__ int world_of_cell(const WorldGrid* g, int nw, int64_t
 // last scene kept as well, binning 64 worlds of 45 K triangles takes 0.35 ms
 // instead of 2.67 (this kernel and the count took 0.69 and 0.55 of them).
 constexpr int kCellLanes = 8;
-__global__ __launch_bounds__(kBlock) void bin_finalize_kernel(BinWork W)
+// Cells of one launch: a grid is limited to 2^32 - 1 threads, a scene to 2^31 - 1 cells.
+constexpr int64_t kCellsPerLaunch = 1ll << 28;
+__global__ __launch_bounds__(kBlock) void bin_finalize_kernel(BinWork W, int64_t c0)
 {
-    const int64_t c = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kCellLanes;
+    const int64_t c = c0 + ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kCellLanes;
     const int sub = threadIdx.x % kCellLanes;
     const bool in = c < W.total_cells;
     uint32_t lo[3] = {0xFF800000u, 0xFF800000u, 0xFF800000u};   // ord(+inf)
@@ -388,8 +390,10 @@ hipError_t launch_bin(const BinWork& W, hipStream_t s)
     hipLaunchKernelGGL(scan_add_kernel, dim3(blocks(n)), dim3(kBlock), 0, s, W.count, n, W.scan_tmp);
     if (W.P > 0)
         hipLaunchKernelGGL(bin_scatter_kernel, dim3(blocks(W.P)), dim3(kBlock), 0, s, W);
-    if (cells > 0)
-        hipLaunchKernelGGL(bin_finalize_kernel, dim3(blocks(cells * kCellLanes)), dim3(kBlock), 0, s, W);
+    for (int64_t c0 = 0; c0 < cells; c0 += kCellsPerLaunch) {
+        const int64_t m = cells - c0 < kCellsPerLaunch ? cells - c0 : kCellsPerLaunch;
+        hipLaunchKernelGGL(bin_finalize_kernel, dim3(blocks(m * kCellLanes)), dim3(kBlock), 0, s, W, c0);
+    }
     hipLaunchKernelGGL(bin_margin_kernel, dim3(blocks(W.num_worlds)), dim3(kBlock), 0, s, W);
     return hipGetLastError();
 }

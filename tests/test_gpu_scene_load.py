@@ -159,3 +159,38 @@ def test_uploads_from_two_threads(lib):
         t.join()
     for k in (0, 1):
         assert torch.equal(out[k][0], ref[k][0]) and torch.equal(out[k][1], ref[k][1])
+
+
+def test_more_cells_than_one_launch_holds(lib):
+    # 23,200 x 23,200 cells and a second world behind them (2^29 cells are 2^32
+    # threads of the cells' boxes): the boxes and margins of the last cells decide
+    # what is drawn around the agents that stand there
+    import torch
+    from oracle import oracle as O
+    from tests.parity import assert_parity
+    from tests.scenes import make_agents, make_rig, quad
+    side, cell = 2320.0, 0.1
+    tris, cls, offs, rows = [], [], [0], []
+    for world, (cx, cy) in enumerate(((side - 60.0, side - 60.0), (30.0, 30.0))):
+        for i in range(-15, 15):
+            for j in range(-15, 15):
+                x, y = cx + 2.0 * i, cy + 2.0 * j
+                tris += quad((x, y, 0.0), (x + 2.0, y, 0.0), (x + 2.0, y + 2.0, 0.0), (x, y + 2.0, 0.0))
+                cls += [1 + (i + j + world) % 5] * 2
+        offs.append(len(tris))
+        rows += [(cx - 20.0, cy, 0.0, 1.0, 0.0, 4.5, 1.9, 1.5, 6), (cx, cy + 3.0, 0.0, 0.8, -0.6, 4.5, 1.9, 1.5, 6)]
+    bounds = np.float32([[0.0, 0.0, side, side], [0.0, 0.0, 60.0, 60.0]])
+    scene = sg.Scene(num_worlds=2, verts=np.asarray(tris, np.float32).reshape(-1, 9), cls=np.asarray(cls, np.uint8),
+                     tri_offsets=np.asarray(offs, np.int64), bounds=bounds)
+    agents, rig = make_agents(rows, num_worlds=2), make_rig(far=25.0, mounts=((0.0, 0.0, 1.5, 1.0, 0.0),))
+    r = lib.Renderer(0)
+    try:
+        r.upload(scene, cell)
+        assert lib.pictura_bins_info(r.ctx, 2)[2] > 1 << 29
+        c, d = r.render(lib.DeviceAgents.from_host(agents), rig)
+        c, d = c.cpu().numpy(), d.cpu().numpy()
+    finally:
+        r.close_checked()
+    ora = O.render(scene, agents, rig)
+    assert np.isfinite(ora["depth"]).mean((1, 2)).min() > 0.4   # ground in every view
+    assert_parity(c.reshape(ora["cls"].shape), d.reshape(ora["cls"].shape), ora, "last cells")
