@@ -539,7 +539,8 @@ static pictura_status render_setup(pictura_ctx c, const pictura_agents* ag, cons
 
 // Launch a render set up by render_setup on stream s, behind the context's
 // last render call if that was on another stream (a caller may step or free
-// the agents on s afterwards, and both calls read them in place).
+// the agents on s afterwards, and both calls read them in place; the outputs
+// may be that call's too, so the counts are cleared behind it as well).
 static hipError_t render_launch(pictura_ctx c, const RenderParams& P, hipStream_t s)
 {
     hipError_t e = hipSuccess;
@@ -548,6 +549,9 @@ static hipError_t render_launch(pictura_ctx c, const RenderParams& P, hipStream_
         return e;
     }
     if (c->order_used && c->order_stream != s && (e = hipStreamWaitEvent(s, c->order_event, 0)) != hipSuccess) return e;
+    if (P.out_counts &&
+        (e = launch_fill_u32(P.out_counts, (size_t)P.num_views * (size_t)P.A * 2u, 0u, s)) != hipSuccess)
+        return e;
     if ((e = launch_render(P, s)) != hipSuccess) return e;
     if ((e = hipEventRecord(c->order_event, s)) != hipSuccess) return e;
     c->order_stream = s;
@@ -616,9 +620,7 @@ pictura_status pictura_render_instances(pictura_ctx c, const pictura_agents* ag,
     if (st != PICTURA_OK || empty) return st;
     P.out_inst = out_inst;
     P.out_counts = out_counts;
-    hipError_t e = launch_fill_u32(out_counts, (size_t)P.num_views * (size_t)P.A * 2u, 0u, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(c, e, "render_instances clear");
-    e = render_launch(c, P, (hipStream_t)stream);
+    hipError_t e = render_launch(c, P, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "render_instances launch");
     return PICTURA_OK;
 }

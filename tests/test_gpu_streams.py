@@ -17,8 +17,7 @@ def _torch():
     return torch
 
 
-def test_render_calls_on_two_streams_keep_their_agents():
-    torch = _torch()
+def _workload():
     from paper_2607_26005_amd import pictura
     wl = sg.make_config(2, num_worlds=4)    # small-batch worlds: 512 views per call
     other = wl.agents.copy()
@@ -29,10 +28,28 @@ def test_render_calls_on_two_streams_keep_their_agents():
     h = rng.uniform(-np.pi, np.pi, other.x.shape)
     other.cos_h = np.cos(h).astype(np.float32)
     other.sin_h = np.sin(h).astype(np.float32)
+    return wl, [pictura.DeviceAgents.from_host(wl.agents), pictura.DeviceAgents.from_host(other)]
+
+
+def _busy(torch, stream, ms=100.0):
+    """Keep `stream` busy for about `ms` milliseconds."""
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(100000)
+        a.record()
+        torch.cuda._sleep(1000000)
+        b.record()
+        b.synchronize()
+        torch.cuda._sleep(int(1e6 * ms / max(a.elapsed_time(b), 1e-3)))
+
+
+def test_render_calls_on_two_streams_keep_their_agents():
+    torch = _torch()
+    from paper_2607_26005_amd import pictura
+    wl, sets = _workload()
     r = pictura.Renderer(0)
     try:
         r.upload(wl.scene, wl.cell_size)
-        sets = [pictura.DeviceAgents.from_host(wl.agents), pictura.DeviceAgents.from_host(other)]
         refs = [tuple(t.clone() for t in r.render(d, wl.rig)) for d in sets]
         torch.cuda.synchronize()
         assert not torch.equal(refs[0][0], refs[1][0])
@@ -45,5 +62,30 @@ def test_render_calls_on_two_streams_keep_their_agents():
         for i, (c, d) in outs:
             assert torch.equal(c, refs[i][0]), f"class image of agent set {i} changed on its stream"
             assert torch.equal(d, refs[i][1]), f"depth image of agent set {i} changed on its stream"
+    finally:
+        r.close_checked()
+
+
+def test_instance_renders_on_two_streams_share_their_outputs():
+    # the second call clears the counts of the same buffers: only behind the
+    # first call's kernel, which adds to them
+    torch = _torch()
+    from paper_2607_26005_amd import pictura
+    wl, sets = _workload()
+    r = pictura.Renderer(0)
+    try:
+        r.upload(wl.scene, wl.cell_size)
+        outs = r.render_instances(sets[0], wl.rig)
+        first = [t.clone() for t in outs]
+        refs = [t.clone() for t in r.render_instances(sets[1], wl.rig)]
+        torch.cuda.synchronize()
+        assert not torch.equal(first[3], refs[3])
+        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        _busy(torch, s1)   # the first call has not begun when the second is queued
+        pictura.pictura_render_instances(r.ctx, sets[0], wl.rig, *outs, stream=s1)
+        pictura.pictura_render_instances(r.ctx, sets[1], wl.rig, *outs, stream=s2)
+        torch.cuda.synchronize()
+        for got, want, name in zip(outs, refs, ("classes", "depths", "instances", "counts")):
+            assert torch.equal(got, want), name
     finally:
         r.close_checked()
