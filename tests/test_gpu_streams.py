@@ -1,7 +1,7 @@
-"""Render calls of one context on two streams.  A call on another stream than
-the previous one is ordered after that call's kernels with an event.
-Different agent sets rendered back to back on two streams must give the images
-each set gives alone."""
+"""Render calls of one context on two streams.  Render kernels read the agents'
+arrays in place, and a call on another stream than the previous one runs behind
+that call's kernels (an event wait on the device): what the second stream does
+afterwards to the first call's agents or outputs cannot reach that call."""
 import numpy as np
 import pytest
 
@@ -87,5 +87,32 @@ def test_instance_renders_on_two_streams_share_their_outputs():
         torch.cuda.synchronize()
         for got, want, name in zip(outs, refs, ("classes", "depths", "instances", "counts")):
             assert torch.equal(got, want), name
+    finally:
+        r.close_checked()
+
+
+def test_render_on_another_stream_waits_for_the_last_one():
+    # agents overwritten on the second stream, behind that stream's own render:
+    # the render on the first stream, which reads them in place, has already ended
+    torch = _torch()
+    from paper_2607_26005_amd import pictura
+    wl, sets = _workload()
+    r = pictura.Renderer(0)
+    try:
+        r.upload(wl.scene, wl.cell_size)
+        refs = [tuple(t.clone() for t in r.render(d, wl.rig)) for d in sets]
+        torch.cuda.synchronize()
+        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        outs = [tuple(torch.empty_like(t) for t in refs[0]) for _ in sets]
+        torch.cuda.synchronize()
+        _busy(torch, s1)
+        r.render(sets[0], wl.rig, *outs[0], stream=s1)
+        r.render(sets[1], wl.rig, *outs[1], stream=s2)
+        with torch.cuda.stream(s2):
+            for f in ("x", "y", "cos_h", "sin_h"):
+                getattr(sets[0], f).copy_(getattr(sets[1], f))
+        torch.cuda.synchronize()
+        for k in (0, 1):
+            assert torch.equal(outs[k][0], refs[k][0]) and torch.equal(outs[k][1], refs[k][1]), k
     finally:
         r.close_checked()
