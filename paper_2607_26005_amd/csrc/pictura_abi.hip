@@ -5,13 +5,20 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
-#include <unordered_map>
 #include <vector>
 
 #include "pictura.h"
 #include "pictura_internal.h"
 
 using namespace pictura;
+
+// A scene or bin array of a context, and the bytes it was allocated with.
+template <typename T>
+struct DevArray {
+    T* p = nullptr;
+    size_t bytes = 0;
+    operator T*() const { return p; }
+};
 
 struct pictura_ctx_s {
     int device = 0;
@@ -21,14 +28,14 @@ struct pictura_ctx_s {
     int64_t T = 0;
     std::vector<int64_t> offsets_h;
     std::vector<float> bounds_h;
-    float* verts = nullptr;
-    uint8_t* cls = nullptr;
-    int64_t* offsets_d = nullptr;
+    DevArray<float> verts;
+    DevArray<uint8_t> cls;
+    DevArray<int64_t> offsets_d;
     // primitives: triangles and triangle pairs (see SceneDev)
     int64_t P = 0;
-    uint32_t* prims = nullptr;        // [P] (room for T) first triangle | kPrimFlagPair
-    uint2* pair_tiles = nullptr;      // scan of the pairing
-    int64_t* prim_offsets_d = nullptr;   // [nw + 1]
+    DevArray<uint32_t> prims;          // [P] (room for T) first triangle | kPrimFlagPair
+    DevArray<uint2> pair_tiles;        // scan of the pairing
+    DevArray<int64_t> prim_offsets_d;   // [nw + 1]
     bool have_scene = false;
     uint8_t max_cls = 0;   // largest class ID of the static triangles
     // bins
@@ -36,20 +43,19 @@ struct pictura_ctx_s {
     float cell_size = 0.0f;
     int64_t total_cells = 0;
     std::vector<WorldGrid> grids_h;
-    std::unordered_map<const void*, size_t> cap;   // bytes of the scene's and bins' allocations, by address
-    WorldGrid* grids = nullptr;
-    uint32_t* home = nullptr;
-    uint32_t* rank = nullptr;
-    uint32_t* cell_start = nullptr;
-    uint32_t* margin_bits = nullptr;
-    uint32_t* scan_tmp = nullptr;
-    float4* primA = nullptr;
-    float4* primB = nullptr;
-    float4* primC = nullptr;
-    float* primD = nullptr;
-    uint32_t* perm = nullptr;
-    float4* cell_lo = nullptr;
-    float4* cell_hi = nullptr;
+    DevArray<WorldGrid> grids;
+    DevArray<uint32_t> home;
+    DevArray<uint32_t> rank;
+    DevArray<uint32_t> cell_start;
+    DevArray<uint32_t> margin_bits;
+    DevArray<uint32_t> scan_tmp;
+    DevArray<float4> primA;
+    DevArray<float4> primB;
+    DevArray<float4> primC;
+    DevArray<float> primD;
+    DevArray<uint32_t> perm;
+    DevArray<float4> cell_lo;
+    DevArray<float4> cell_hi;
     // options
     int cull = 1;
     int tile = 0;
@@ -163,17 +169,17 @@ hipError_t dalloc(T*& p, size_t count)
 }
 
 template <typename T>
-void sfree(pictura_ctx c, T*& p)
+void sfree(DevArray<T>& a)
 {
-    if (p) c->cap.erase((const void*)p);
-    dfree(p);
+    dfree(a.p);
+    a.bytes = 0;
 }
 
 void free_bins(pictura_ctx c)
 {
-    sfree(c, c->grids); sfree(c, c->home); sfree(c, c->rank); sfree(c, c->cell_start);
-    sfree(c, c->margin_bits); sfree(c, c->scan_tmp); sfree(c, c->primA); sfree(c, c->primB); sfree(c, c->primC);
-    sfree(c, c->primD); sfree(c, c->perm); sfree(c, c->cell_lo); sfree(c, c->cell_hi);
+    sfree(c->grids); sfree(c->home); sfree(c->rank); sfree(c->cell_start);
+    sfree(c->margin_bits); sfree(c->scan_tmp); sfree(c->primA); sfree(c->primB); sfree(c->primC);
+    sfree(c->primD); sfree(c->perm); sfree(c->cell_lo); sfree(c->cell_hi);
     c->binned = false;
     c->total_cells = 0;
     c->grids_h.clear();
@@ -184,28 +190,25 @@ void free_bins(pictura_ctx c)
 // maps of like size allocates nothing; a much smaller scene gives the memory
 // back).  The caller has waited for the device, so nothing still reads it.
 template <typename T>
-hipError_t salloc(pictura_ctx c, T*& p, size_t count)
+hipError_t salloc(DevArray<T>& a, size_t count)
 {
     const size_t need = (count ? count : 1) * sizeof(T);
-    if (p) {
-        const auto it = c->cap.find((const void*)p);
-        if (it != c->cap.end() && it->second >= need && it->second / 4 <= need) return hipSuccess;
-        sfree(c, p);
-    }
-    hipError_t e = hipMalloc((void**)&p, need);
+    if (a.p && a.bytes >= need && a.bytes / 4 <= need) return hipSuccess;
+    sfree(a);
+    const hipError_t e = hipMalloc((void**)&a.p, need);
     if (e != hipSuccess) {
-        p = nullptr;
+        a.p = nullptr;
         return e;
     }
-    c->cap[(const void*)p] = need;
+    a.bytes = need;
     return hipSuccess;
 }
 
 void free_scene(pictura_ctx c)
 {
     free_bins(c);
-    sfree(c, c->verts); sfree(c, c->cls); sfree(c, c->offsets_d); dfree(c->stats);
-    sfree(c, c->prims); sfree(c, c->prim_offsets_d); sfree(c, c->pair_tiles);
+    sfree(c->verts); sfree(c->cls); sfree(c->offsets_d); dfree(c->stats);
+    sfree(c->prims); sfree(c->prim_offsets_d); sfree(c->pair_tiles);
     c->have_scene = false;
     c->T = 0;
     c->P = 0;
@@ -325,10 +328,10 @@ pictura_status pictura_scene_upload(pictura_ctx c, const pictura_scene* s, void*
     dfree(c->stats);
     auto alloc = [&]() {
         hipError_t a;
-        (void)((a = salloc(c, c->prims, (size_t)T)) != hipSuccess || (a = salloc(c, c->prim_offsets_d, (size_t)nw + 1)) != hipSuccess ||
-               (a = salloc(c, c->pair_tiles, (size_t)pair_tiles_needed(T))) != hipSuccess ||
-               (a = salloc(c, c->verts, (size_t)T * 9)) != hipSuccess || (a = salloc(c, c->cls, (size_t)T)) != hipSuccess ||
-               (a = salloc(c, c->offsets_d, (size_t)nw + 1)) != hipSuccess);
+        (void)((a = salloc(c->prims, (size_t)T)) != hipSuccess || (a = salloc(c->prim_offsets_d, (size_t)nw + 1)) != hipSuccess ||
+               (a = salloc(c->pair_tiles, (size_t)pair_tiles_needed(T))) != hipSuccess ||
+               (a = salloc(c->verts, (size_t)T * 9)) != hipSuccess || (a = salloc(c->cls, (size_t)T)) != hipSuccess ||
+               (a = salloc(c->offsets_d, (size_t)nw + 1)) != hipSuccess);
         return a;
     };
     if ((e = alloc()) != hipSuccess) {
@@ -400,13 +403,13 @@ pictura_status pictura_bin_scene(pictura_ctx c, float cell, void* stream)
     const int64_t ntmp = scan_tmp_needed(total + 1);
     auto alloc = [&]() {
         hipError_t a;
-        (void)((a = salloc(c, c->grids, (size_t)nw)) != hipSuccess || (a = salloc(c, c->home, (size_t)P)) != hipSuccess ||
-               (a = salloc(c, c->rank, (size_t)P)) != hipSuccess || (a = salloc(c, c->cell_start, (size_t)total + 1)) != hipSuccess ||
-               (a = salloc(c, c->margin_bits, (size_t)nw)) != hipSuccess ||
-               (a = salloc(c, c->scan_tmp, (size_t)ntmp)) != hipSuccess || (a = salloc(c, c->primA, (size_t)P)) != hipSuccess ||
-               (a = salloc(c, c->primB, (size_t)P)) != hipSuccess || (a = salloc(c, c->primC, (size_t)P)) != hipSuccess ||
-               (a = salloc(c, c->primD, (size_t)P)) != hipSuccess || (a = salloc(c, c->perm, (size_t)P)) != hipSuccess ||
-               (a = salloc(c, c->cell_lo, (size_t)total)) != hipSuccess || (a = salloc(c, c->cell_hi, (size_t)total)) != hipSuccess);
+        (void)((a = salloc(c->grids, (size_t)nw)) != hipSuccess || (a = salloc(c->home, (size_t)P)) != hipSuccess ||
+               (a = salloc(c->rank, (size_t)P)) != hipSuccess || (a = salloc(c->cell_start, (size_t)total + 1)) != hipSuccess ||
+               (a = salloc(c->margin_bits, (size_t)nw)) != hipSuccess ||
+               (a = salloc(c->scan_tmp, (size_t)ntmp)) != hipSuccess || (a = salloc(c->primA, (size_t)P)) != hipSuccess ||
+               (a = salloc(c->primB, (size_t)P)) != hipSuccess || (a = salloc(c->primC, (size_t)P)) != hipSuccess ||
+               (a = salloc(c->primD, (size_t)P)) != hipSuccess || (a = salloc(c->perm, (size_t)P)) != hipSuccess ||
+               (a = salloc(c->cell_lo, (size_t)total)) != hipSuccess || (a = salloc(c->cell_hi, (size_t)total)) != hipSuccess);
         return a;
     };
     if ((e = alloc()) != hipSuccess) {
