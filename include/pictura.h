@@ -151,6 +151,9 @@ const char* pictura_last_error(pictura_ctx ctx);
 /* Copy the static scene to device memory owned by the context (replacing any
  * previous scene and invalidating its bins).  Enqueued on `stream`; the host
  * arrays may be reused as soon as the call returns (the copy is staged).
+ * Device memory of the scene before and of its bins is used again where the
+ * new scene is of like size (a context then keeps at most 1.5 times what its
+ * scene needs); otherwise it is freed before any is allocated.
  * EINVAL: null pointers, num_worlds < 1, offsets not non-decreasing, a class
  * ID of 255.  ERANGE: more than 2^31 - 1 triangles.  ENOMEM: allocation. */
 pictura_status pictura_scene_upload(pictura_ctx ctx, const pictura_scene* scene, void* stream);

@@ -185,19 +185,28 @@ void free_bins(pictura_ctx c)
     c->grids_h.clear();
 }
 
-// `count` elements of a scene or bin array: the allocation of the scene before
-// where it is large enough and not over four times as large (a reset with
-// maps of like size allocates nothing; a much smaller scene gives the memory
-// back).  The caller has waited for the device, so nothing still reads it.
+// Scene and bin arrays outlive one scene where the next one is of like size:
+// an array is used again for `count` elements if it holds them and at most half
+// as many bytes again (a reset with such maps allocates nothing, and a context
+// keeps at most 1.5 times what its scene needs).  The caller has waited for
+// the device, so nothing still reads it.
+template <typename T>
+bool holds(const DevArray<T>& a, size_t count)
+{
+    const size_t need = (count ? count : 1) * sizeof(T);
+    return a.p && a.bytes >= need && a.bytes - need <= need / 2;
+}
+
 template <typename T>
 hipError_t salloc(DevArray<T>& a, size_t count)
 {
-    const size_t need = (count ? count : 1) * sizeof(T);
-    if (a.p && a.bytes >= need && a.bytes / 4 <= need) return hipSuccess;
+    if (holds(a, count)) return hipSuccess;
     sfree(a);
+    const size_t need = (count ? count : 1) * sizeof(T);
     const hipError_t e = hipMalloc((void**)&a.p, need);
     if (e != hipSuccess) {
         a.p = nullptr;
+        (void)hipGetLastError();   // reported here, not by the next launch
         return e;
     }
     a.bytes = need;
@@ -326,19 +335,15 @@ pictura_status pictura_scene_upload(pictura_ctx c, const pictura_scene* s, void*
     c->have_scene = false;
     c->binned = false;
     dfree(c->stats);
-    auto alloc = [&]() {
-        hipError_t a;
-        (void)((a = salloc(c->prims, (size_t)T)) != hipSuccess || (a = salloc(c->prim_offsets_d, (size_t)nw + 1)) != hipSuccess ||
-               (a = salloc(c->pair_tiles, (size_t)pair_tiles_needed(T))) != hipSuccess ||
-               (a = salloc(c->verts, (size_t)T * 9)) != hipSuccess || (a = salloc(c->cls, (size_t)T)) != hipSuccess ||
-               (a = salloc(c->offsets_d, (size_t)nw + 1)) != hipSuccess);
-        return a;
+    auto arrays = [&](auto&& f) {
+        return f(c->prims, (size_t)T) && f(c->prim_offsets_d, (size_t)nw + 1) && f(c->pair_tiles, (size_t)pair_tiles_needed(T)) &&
+               f(c->verts, (size_t)T * 9) && f(c->cls, (size_t)T) && f(c->offsets_d, (size_t)nw + 1);
     };
-    if ((e = alloc()) != hipSuccess) {
-        // once more without the last scene's arrays and bins
-        (void)hipGetLastError();
+    // a scene of another size starts from nothing: what is held and what it needs never add up
+    if (!arrays([](auto& a, size_t n) { return holds(a, n); })) free_scene(c);
+    if (!arrays([&](auto& a, size_t n) { return (e = salloc(a, n)) == hipSuccess; })) {
         free_scene(c);
-        if ((e = alloc()) != hipSuccess) { free_scene(c); return hip_fail(c, e, "scene_upload alloc"); }
+        return hip_fail(c, e, "scene_upload alloc");
     }
     int64_t P = 0;
     PairWork W{c->verts, c->cls, c->offsets_d, T, nw, c->pair_tiles, c->prims, c->prim_offsets_d};
@@ -401,21 +406,16 @@ pictura_status pictura_bin_scene(pictura_ctx c, float cell, void* stream)
     if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(c, e, "bin_scene sync");
     c->binned = false;
     const int64_t ntmp = scan_tmp_needed(total + 1);
-    auto alloc = [&]() {
-        hipError_t a;
-        (void)((a = salloc(c->grids, (size_t)nw)) != hipSuccess || (a = salloc(c->home, (size_t)P)) != hipSuccess ||
-               (a = salloc(c->rank, (size_t)P)) != hipSuccess || (a = salloc(c->cell_start, (size_t)total + 1)) != hipSuccess ||
-               (a = salloc(c->margin_bits, (size_t)nw)) != hipSuccess ||
-               (a = salloc(c->scan_tmp, (size_t)ntmp)) != hipSuccess || (a = salloc(c->primA, (size_t)P)) != hipSuccess ||
-               (a = salloc(c->primB, (size_t)P)) != hipSuccess || (a = salloc(c->primC, (size_t)P)) != hipSuccess ||
-               (a = salloc(c->primD, (size_t)P)) != hipSuccess || (a = salloc(c->perm, (size_t)P)) != hipSuccess ||
-               (a = salloc(c->cell_lo, (size_t)total)) != hipSuccess || (a = salloc(c->cell_hi, (size_t)total)) != hipSuccess);
-        return a;
+    auto arrays = [&](auto&& f) {
+        const size_t np = (size_t)P, nc = (size_t)total;
+        return f(c->grids, (size_t)nw) && f(c->home, np) && f(c->rank, np) && f(c->cell_start, nc + 1) &&
+               f(c->margin_bits, (size_t)nw) && f(c->scan_tmp, (size_t)ntmp) && f(c->primA, np) && f(c->primB, np) &&
+               f(c->primC, np) && f(c->primD, np) && f(c->perm, np) && f(c->cell_lo, nc) && f(c->cell_hi, nc);
     };
-    if ((e = alloc()) != hipSuccess) {
-        (void)hipGetLastError();
+    if (!arrays([](auto& a, size_t n) { return holds(a, n); })) free_bins(c);   // (as the scene's)
+    if (!arrays([&](auto& a, size_t n) { return (e = salloc(a, n)) == hipSuccess; })) {
         free_bins(c);
-        if ((e = alloc()) != hipSuccess) { free_bins(c); return hip_fail(c, e, "bin_scene alloc"); }
+        return hip_fail(c, e, "bin_scene alloc");
     }
     if ((e = hipMemcpyAsync(c->grids, grids.data(), sizeof(WorldGrid) * nw, hipMemcpyHostToDevice, st)) != hipSuccess) {
         free_bins(c);

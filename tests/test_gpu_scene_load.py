@@ -132,6 +132,39 @@ def test_reused_memory_between_scenes(lib):
         r.close_checked()
 
 
+def test_memory_of_a_smaller_scene(lib):
+    # after a scene, one of 0.45 of its triangles and cells: the context holds at
+    # most 1.5 times what a fresh one holds for it (allocations come in pages of 2 MiB)
+    import torch
+
+    def scene(n, side):
+        v = np.random.default_rng(n).uniform(-side, side, (n, 9)).astype(np.float32)
+        return sg.Scene(num_worlds=1, verts=v, cls=np.ones(n, np.uint8), tri_offsets=np.asarray([0, n], np.int64),
+                        bounds=np.float32([[-side, -side, side, side]]))
+
+    def held():
+        torch.cuda.synchronize()
+        return -torch.cuda.mem_get_info()[0]
+    big, small = scene(2_000_000, 1000.0), scene(900_000, 670.0)
+    warm = lib.Renderer(0)
+    warm.upload(small, 1.0)
+    warm.close_checked()
+    base = held()
+    f = lib.Renderer(0)
+    f.upload(small, 1.0)
+    fresh = held() - base
+    f.close_checked()
+    base = held()
+    r = lib.Renderer(0)
+    try:
+        r.upload(big, 1.0)
+        assert held() - base > 2 * fresh
+        r.upload(small, 1.0)
+        assert 0 < held() - base <= 1.5 * fresh + (40 << 20), (held() - base, fresh)
+    finally:
+        r.close_checked()
+
+
 def test_uploads_from_two_threads(lib):
     import threading
     import torch
