@@ -28,7 +28,7 @@
  *    host and returned synchronously without launching anything; the context
  *    stays usable after any error.  pictura_last_error() gives a message.
  *  - Work is enqueued on `stream` and the calls return without synchronising,
- *    except where a call says it copies to host memory.
+ *    except where a call says that it waits or copies to host memory.
  *  - A context is not thread-safe: use one context per host thread.
  *  - Render kernels read the agents' arrays in place.  A render call on another
  *    stream than the previous render call of the context is ordered after that
@@ -149,8 +149,10 @@ void pictura_destroy(pictura_ctx ctx);
 const char* pictura_last_error(pictura_ctx ctx);
 
 /* Copy the static scene to device memory owned by the context (replacing any
- * previous scene and invalidating its bins).  Enqueued on `stream`; the host
- * arrays may be reused as soon as the call returns (the copy is staged).
+ * previous scene and invalidating its bins).  Enqueued on `stream`, which the
+ * call waits for; where it replaces a scene it first waits for the whole device,
+ * as a render on any stream may read that.  The host arrays may be reused as
+ * soon as the call returns.
  * Device memory of the scene before and of its bins is used again where the
  * new scene is of like size (a context then keeps at most 1.5 times what its
  * scene needs); otherwise it is freed before any is allocated.
@@ -164,7 +166,8 @@ pictura_status pictura_scene_upload(pictura_ctx ctx, const pictura_scene* scene,
  * box (clamped into the grid); each cell records its triangle range and the
  * 3-D bounding box of its triangles.  The library re-lays the triangles out
  * in cell order.  ESTATE: no scene.  EINVAL: cell_size_m not > 0.
- * ERANGE: more than 2^31 - 1 cells.  Enqueued on `stream`. */
+ * ERANGE: more than 2^31 - 1 cells.  Enqueued on `stream`, which the call waits
+ * for; where it replaces the scene's bins it first waits for the whole device. */
 pictura_status pictura_bin_scene(pictura_ctx ctx, float cell_size_m, void* stream);
 
 /* Render all V = num_worlds * agents_per_world * num_cams views (paper

@@ -331,7 +331,7 @@ pictura_status pictura_scene_upload(pictura_ctx c, const pictura_scene* s, void*
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
     // nothing on the device still reads the scene whose arrays are reused or freed
-    if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(c, e, "scene_upload sync");
+    if (c->verts && (e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(c, e, "scene_upload sync");
     c->have_scene = false;
     c->binned = false;
     dfree(c->stats);
@@ -403,7 +403,8 @@ pictura_status pictura_bin_scene(pictura_ctx c, float cell, void* stream)
     const int64_t P = c->P;
     hipError_t e = hipSuccess;
     // nothing on the device still reads the bins whose arrays are reused or freed
-    if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(c, e, "bin_scene sync");
+    // (the upload has waited where bins of the scene before are left)
+    if (c->binned && (e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(c, e, "bin_scene sync");
     c->binned = false;
     const int64_t ntmp = scan_tmp_needed(total + 1);
     auto arrays = [&](auto&& f) {

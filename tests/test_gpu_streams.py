@@ -2,6 +2,8 @@
 arrays in place, and a call on another stream than the previous one runs behind
 that call's kernels (an event wait on the device): what the second stream does
 afterwards to the first call's agents or outputs cannot reach that call."""
+import time
+
 import numpy as np
 import pytest
 
@@ -115,4 +117,41 @@ def test_render_on_another_stream_waits_for_the_last_one():
         for k in (0, 1):
             assert torch.equal(outs[k][0], refs[k][0]) and torch.equal(outs[k][1], refs[k][1]), k
     finally:
+        r.close_checked()
+
+
+def test_first_scene_of_a_context_waits_for_its_stream_only():
+    torch = _torch()
+    from paper_2607_26005_amd import pictura
+    wl, sets = _workload()
+    w = pictura.Renderer(0)   # kernels loaded, streams in use
+    r = pictura.Renderer(0)
+    try:
+        w.upload(wl.scene, wl.cell_size)
+        refs = w.render(sets[0], wl.rig)
+        busy = torch.cuda.Stream()
+        tiny = torch.zeros(1, device="cuda")
+        torch.cuda.synchronize()
+        _busy(torch, busy, 1000.0)
+        for _ in range(8):   # a stream that does not share the busy one's hardware queue
+            s = torch.cuda.Stream()
+            e = torch.cuda.Event()
+            with torch.cuda.stream(s):
+                tiny.add_(1.0)
+                e.record()
+            for _ in range(100):
+                if e.query():
+                    break
+                time.sleep(0.0002)
+            if e.query():
+                break
+        assert not busy.query(), "a stream that runs beside the busy one"
+        r.upload(wl.scene, wl.cell_size, stream=s)
+        out = r.render(sets[0], wl.rig, stream=s)
+        s.synchronize()
+        assert not busy.query()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], refs[0]) and torch.equal(out[1], refs[1])
+    finally:
+        w.close_checked()
         r.close_checked()
