@@ -43,6 +43,7 @@ class ViewEncoder(nn.Module):
         inv = torch.reciprocal(depth).unsqueeze(1)   # +inf (sky) -> 0
         return torch.cat([onehot, inv], 1)
 
+    @torch.jit.unused
     def _native(self, cls: torch.Tensor, depth: torch.Tensor) -> bool:
         """Whether the library's inference kernels compute this call: plain fp32
         weights of the shapes built above, rendered views on the device, nothing
@@ -91,19 +92,24 @@ class ViewEncoder(nn.Module):
             return False
         return not torch.is_grad_enabled() or not (depth.requires_grad or any(p.requires_grad for p in params))
 
+    @torch.jit.unused
+    def _encode_native(self, cls: torch.Tensor, depth: torch.Tensor) -> torch.Tensor:
+        from paper_2607_26005_amd import pictura
+        a = self.attn
+        with torch.cuda.device(cls.device):
+            out = torch.empty((cls.shape[0], self.width), dtype=torch.float32, device=cls.device)
+            pictura.pictura_encode_views(self.cams, self.num_classes, [(c.weight, c.bias) for c in self.convs],
+                                         self.queries, (a.in_proj_weight, a.in_proj_bias),
+                                         (a.out_proj.weight, a.out_proj.bias), (self.proj.weight, self.proj.bias),
+                                         cls, depth, out)
+        return out.reshape(cls.shape[0] // self.cams, self.cams * self.width)
+
     def forward(self, cls: torch.Tensor, depth: torch.Tensor) -> torch.Tensor:
         """cls, depth: [egos * cams, H, W], view v = ego * cams + camera.  Returns the
         [egos, cams * width] scene embedding (mean of each camera's pooled tokens)."""
-        if self._native(cls, depth):
-            from paper_2607_26005_amd import pictura
-            a = self.attn
-            with torch.cuda.device(cls.device):
-                out = torch.empty((cls.shape[0], self.width), dtype=torch.float32, device=cls.device)
-                pictura.pictura_encode_views(self.cams, self.num_classes, [(c.weight, c.bias) for c in self.convs],
-                                             self.queries, (a.in_proj_weight, a.in_proj_bias),
-                                             (a.out_proj.weight, a.out_proj.bias), (self.proj.weight, self.proj.bias),
-                                             cls, depth, out)
-            return out.reshape(cls.shape[0] // self.cams, self.cams * self.width)
+        if not torch.jit.is_scripting():   # (a scripted module holds the layers alone)
+            if self._native(cls, depth):
+                return self._encode_native(cls, depth)
         x = self.planes(cls, depth)
         for conv in self.convs:
             x = F.relu(conv(x))
