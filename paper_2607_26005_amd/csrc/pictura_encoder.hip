@@ -44,8 +44,8 @@ constexpr int kKC = 32;                           // input channels of one stage
 __device__ __forceinline__ uint32_t div31(uint32_t n, Div31 d) { return d.m ? (__umulhi(n, d.m) >> d.s) : n; }
 
 // x = hi + mid + lo exactly (each the leading 8 significant bits of what is
-// left, by truncation, so no part overflows); an infinity or NaN stays whole in
-// hi.
+// left, by truncation, so no part overflows and all have x's sign); an
+// infinity or NaN stays whole in hi.
 __device__ __forceinline__ void split3(float x, uint32_t& hi, uint32_t& mid, uint32_t& lo)
 {
     const uint32_t u = __float_as_uint(x);
@@ -90,7 +90,16 @@ __device__ void prep_conv(const float* w, uint16_t* o, int cin, int cout, int64_
     const int ch = (int)(i / kKC / cout % (cin / kKC));
     const int tap = (int)(i / kKC / cout / (cin / kKC));
     uint32_t h, m, l;
-    split3(w[((int64_t)n * cin + ch * kKC + k) * kTaps + tap], h, m, l);
+    const float x = w[((int64_t)n * cin + ch * kKC + k) * kTaps + tap];
+    split3(x, h, m, l);
+    // An infinite pixel times a part that is zero would be a NaN beside the infinite
+    // products of the other parts: such parts take the least normal number, of
+    // the weight's sign (2^-126, below 2^-26 of any weight it is added to).
+    if (fabsf(x) >= 0x1p-100f && fabsf(x) < INFINITY) {
+        const uint32_t least = (h & 0x80000000u) | 0x00800000u;
+        if (!(m << 1)) m = least;
+        if (!(l << 1)) l = least;
+    }
     uint16_t* b = o + ((int64_t)(tap * (cin / kKC) + ch) * 3 * cout + n) * kKC + k;
     b[0] = (uint16_t)(h >> 16);
     b[(int64_t)cout * kKC] = (uint16_t)(m >> 16);

@@ -95,6 +95,29 @@ def test_native_encoder_matches_float64(V, H, W, cams):
     assert (got - ref).norm() / ref.norm() < 2.0 ** -22, ((got - ref).norm() / ref.norm()).item()
 
 
+@pytest.mark.parametrize("layer", [1, 2, 3, 4])
+def test_native_encoder_infinite_activations(layer):
+    # A depth of 0 makes infinite activations; weights of 8 significant bits have
+    # no second and third part.  Convolution `layer` takes the infinities in with
+    # negative weights, so its ReLU ends them and the embedding is finite.
+    torch = _torch()
+    from paper_2607_26005_amd.encoder import ViewEncoder
+    torch.manual_seed(layer)
+    enc = ViewEncoder(cams=2).cuda().eval()
+    cls, depth = _views(torch, 4, 40, 56)
+    depth[:, ::17, ::13] = 0.0
+    with torch.no_grad():
+        for k, conv in enumerate(enc.convs):
+            conv.weight.fill_(-2.0 ** -7 if k == layer else 2.0 ** -7)
+            if k == layer:
+                conv.bias.fill_(8.0)
+        assert enc._native(cls, depth)
+        got = enc(cls, depth).cpu().double()
+        ref = _exact(torch, enc, cls, depth)
+    assert torch.isfinite(ref).all()
+    assert (got - ref).norm() / ref.norm() < 2.0 ** -20   # two-part products are exact here: fp32 sums
+
+
 def test_native_encoder_in_parts_and_in_a_graph():
     torch = _torch()
     from paper_2607_26005_amd.encoder import ViewEncoder
