@@ -95,6 +95,38 @@ def test_native_encoder_matches_float64(V, H, W, cams):
     assert (got - ref).norm() / ref.norm() < 2.0 ** -22, ((got - ref).norm() / ref.norm()).item()
 
 
+@pytest.mark.parametrize("V, H, W", [(64, 8, 8), (16, 54, 96)])
+@pytest.mark.parametrize("weights", ["random", "positive", "low bits"])
+def test_native_convolutions_match_float64(V, H, W, weights):
+    # The convolutions alone: queries of zero weigh all tokens alike, and the
+    # projections pass their mean through.  Positive weights let no errors cancel
+    # between products, and with all low mantissa bits set each product leaves out
+    # as much as it can: 1.3e-7 in all (a plain fp32 chain: 1.4e-7), against 6e-7
+    # were the parts of both factors cut to one side.
+    torch = _torch()
+    from paper_2607_26005_amd.encoder import ViewEncoder
+    torch.manual_seed(5)
+    enc = ViewEncoder(cams=1).cuda().eval()
+    cls, depth = _views(torch, V, H, W)
+    with torch.no_grad():
+        enc.queries.zero_()
+        for p in (enc.attn.in_proj_bias, enc.attn.out_proj.bias, enc.proj.bias):
+            p.zero_()
+        enc.attn.in_proj_weight.copy_(torch.eye(128).repeat(3, 1))
+        for p in (enc.attn.out_proj.weight, enc.proj.weight):
+            p.copy_(torch.eye(128))
+        if weights != "random":
+            for conv in enc.convs:
+                conv.weight.abs_()
+                conv.bias.abs_()
+                if weights == "low bits":
+                    conv.weight.view(torch.int32).bitwise_or_(0xFFFF).bitwise_and_(~0x7F0000)
+        assert enc._native(cls, depth)
+        got = enc(cls, depth).cpu().double()
+        ref = _exact(torch, enc, cls, depth)
+    assert (got - ref).norm() / ref.norm() < 2.0 ** -22
+
+
 @pytest.mark.parametrize("layer", [1, 2, 3, 4])
 def test_native_encoder_infinite_activations(layer):
     # A depth of 0 makes infinite activations; weights of 8 significant bits have
