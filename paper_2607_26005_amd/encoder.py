@@ -59,6 +59,16 @@ class ViewEncoder(nn.Module):
         if (V == 0 or V % self.cams or not (1 <= H <= 4096 and 1 <= W <= 4096) or not 1 <= self.cams <= 4096
                 or not 1 <= self.num_classes <= 32):
             return False
+        # One workgroup attends over a view's whole feature map, three times: few
+        # large maps leave the chip idle, and from about 30,000 tokens the passes
+        # come from memory.  Against the layers, views of 256x256 (1,024 tokens)
+        # take 0.83 of the time for one and 0.94 for four, of 288x288 1.03 for two
+        # and 1.05 for eight, of 512x512 1.16 for 8 and 0.77 for 24, of 1024x1024
+        # (16,384) 1.03 for 16, 0.84 for 24 and 0.80 for 96, of 1920x1080 1.22-1.29
+        # for 32-128, of 2048x2048 2.1.
+        tokens = -(-H // 8) * -(-W // 8)
+        if tokens > 1024 and (V < 24 or tokens > 16384):
+            return False
         if (torch.compiler.is_compiling() or torch.jit.is_tracing() or torch.is_autocast_enabled("cuda")
                 or torch._C._len_torch_dispatch_stack() or torch._C._len_torch_function_stack()
                 or torch._C._functorch.peek_interpreter_stack() is not None

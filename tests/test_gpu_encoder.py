@@ -210,3 +210,22 @@ def test_encoder_other_uses_take_the_layers():
         assert y.shape == (1, 256)
         v = torch.func.vmap(lambda c, d: enc.planes(c, d))(cls.unsqueeze(1), depth.unsqueeze(1))
         assert v.shape == (4, 1, 12, 20, 24)
+
+
+@pytest.mark.parametrize("V, H, W, native", [(4, 256, 256, True), (4, 264, 257, False), (20, 264, 256, False),
+                                             (24, 264, 256, True), (24, 1024, 1024, True), (24, 1025, 1024, False)])
+def test_few_large_views_take_the_layers(V, H, W, native):
+    # where one workgroup per view is slower than the layers; the same embedding either way
+    torch = _torch()
+    from paper_2607_26005_amd.encoder import ViewEncoder
+    torch.manual_seed(6)
+    enc = ViewEncoder().cuda().eval()
+    cls, depth = _views(torch, V, H, W)
+    with torch.no_grad():
+        assert enc._native(cls, depth) == native
+        x = enc.planes(cls[:4], depth[:4])
+        for conv in enc.convs:
+            x = torch.relu(conv(x))
+        tok = x.flatten(2).transpose(1, 2).contiguous()
+        ref = enc.proj(enc.attn(enc.queries, tok, tok, need_weights=False)[0].mean(1)).reshape(1, -1)
+        assert torch.allclose(enc(cls, depth)[:1], ref, rtol=1e-5, atol=1e-6)
