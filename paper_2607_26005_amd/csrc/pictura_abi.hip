@@ -73,6 +73,9 @@ struct pictura_ctx_s {
 
 namespace {
 
+// the images of a render call, numbered as the kernels' modes
+enum { kModeClass = 0, kModeInst = 1, kModeAA = 2, kModeRgb = 3 };
+
 pictura_status fail(pictura_ctx c, pictura_status st, const char* fmt, ...)
 {
     char buf[512];
@@ -94,32 +97,57 @@ int even_part(int n, int count, int unit)
 
 // Tile of a W x H view.  As few tiles of at most 64x64 as the view needs, split
 // evenly (96 wide: two of 48 rather than 64 and 32), their width a multiple of
-// 16 or of 4 (the vector write-out's units) when the view's is one.  A wider or
-// taller tile is taken only where the framebuffer then holds the view in fewer
-// tiles, as each tile gathers and culls for itself: 100x75 is two tiles of
-// 100x38 instead of four of 52x38 (12,288 colour views: 531 us against 623), and
-// only in launches of at least three rounds of resident tiles: in shorter ones
-// the larger tiles' tail weighs more (class/depth views of 65x65 in two wide
-// tiles or four: 1,536 views 80 us against 79, 3,072 views 121 against 137;
-// 100x75: 1,536 views 103 against 90, 3,072 views 146 against 158).  With
-// equal counts the 64x64 limit stays: its kernels keep more in registers (128x128
-// views: 855 us in 64x64 tiles, 1,052 in 128x32).
+// 16 or of 4 (the vector write-out's units) when the view's is one.  Wider or
+// taller tiles are taken where they are fewer by a third, as each tile gathers
+// and culls for itself, in launches of three rounds of resident tiles or more:
+// in shorter ones the larger tiles' tail weighs more.  Columns of the view's
+// whole height share the work evenly, rows do not (sky above, map below), and
+// in the modes with the dearer tiles rows take four rounds.  Time in such tiles
+// over time in 64x64 ones, class/depth - colour - antialiased - instances, on
+// maps without walls:
+//   100x40, 2 tiles -> 1: 6,208 views 0.90 - 0.88 - 0.95 - 0.99, 25,984 views
+//   0.82 - 0.83 - 0.87 - 0.84;
+//   130x50, 3 -> 2 columns: 3,072 views 0.95 - 0.97 - 1.00 - 0.96, 12,992 views
+//   0.91 - 0.95 - 0.95 - 0.95;
+//   136x76, 6 -> 3 columns: 2,048 views 0.94 - 0.95 - 0.93 - 0.96;
+//   100x75, 4 -> 2 rows: 3,328 views 1.01 - 1.03 - 1.06 - 1.11, 65x65 there 0.96
+//   - 0.98 - 1.01 - 1.03, 12,992 views 0.88 - 0.87 - 0.90 - 0.90;
+//   160x90, 6 -> 4: 1,536 views 0.98 - 1.00 - 1.02 - 1.12, 6,528 views 0.93 -
+//   0.94 - 0.96 - 0.97;
+//   100x100, 4 -> 3 rows: 8,640 views 1.04 - 1.06 - 1.05 - 1.04, and of six sizes
+//   with 3 to 75 such tiles in launches of 12,000 to 26,000 tiles 1.04 - 1.03 -
+//   1.03 - 0.99 in the mean;
+//   150x100, 6 -> 5 columns: 5,184 views 1.11 - 1.13 - 1.07 - 1.15.
+// So less than a third is worth it for instances from six rounds on, in rows.
+// Traffic lights stand in built-up maps, whose tiles hold more and whose lights
+// every tile culls as well.  There columns pay when they are fewer at all
+// (150x100, 6 -> 5: 2,496 views 0.93 - 0.97 - 0.95 - 1.01; 96x96, 4 -> 3: 3,008
+// views 0.92 - 0.95 - 0.89 - 1.00), rows from six rounds on but for antialiasing
+// (120x67, 4 -> 3: 6,656 views 0.97 - 0.99 - 1.01 - 0.95, 2,048 views 1.02 - 1.05
+// - 1.09 - 1.01), and three rounds do in every mode (100x75: 3,072 views 0.94 -
+// 0.94 - 0.97 - 0.93).
+// With equal counts the 64x64 limit stays: its kernels keep more in registers
+// (128x128 views: 855 us in 64x64 tiles, 1,052 in 128x32).
 constexpr int64_t kResidentTiles = 2048;   // eight workgroups on each of 256 CUs
-void choose_tile(int64_t views, int W, int H, int& tw, int& th)
+void choose_tile(int64_t views, int W, int H, int mode, bool lights, int& tw, int& th)
 {
     const int unit = (W % 16) == 0 ? 16 : (W % 4) == 0 ? 4 : 1;
     const int nx0 = (W + 63) / 64, ny0 = (H + 63) / 64;
     tw = even_part(W, nx0, unit);
     if (tw > 64) tw = (W + nx0 - 1) / nx0;
     th = (H + ny0 - 1) / ny0;
-    int best = nx0 * ny0, words = 0;
+    const int narrow = nx0 * ny0;
+    int best = narrow, words = 0;
     for (int nx = (W + kTileMax - 1) / kTileMax; nx < best; ++nx) {
         const int w = even_part(W, nx, unit);
         if (w > kTileMax) continue;
         int ny = (H + kTileMax - 1) / kTileMax;
         while (nx * ny < best && tile_words(w, (H + ny - 1) / ny) > kTileWords) ++ny;
         const int h = (H + ny - 1) / ny, n = nx * ny;
-        if (views * n < 3 * kResidentTiles) continue;
+        const bool third = 3 * n <= 2 * narrow, rows = ny > 1;
+        if (!third && !(lights ? !rows || mode != kModeAA : rows && mode == kModeInst)) continue;
+        const int rounds = !rows ? 3 : !third ? 6 : !lights && (mode == kModeInst || mode == kModeAA) ? 4 : 3;
+        if (views * n < rounds * kResidentTiles) continue;
         if (tile_words(w, h) > kTileWords || n > best || (n == best && (words == 0 || tile_words(w, h) >= words))) continue;
         tw = w;
         th = h;
@@ -442,7 +470,7 @@ pictura_status pictura_bin_scene(pictura_ctx c, float cell, void* stream)
 
 // Argument checks and the parameter block of one render call; the launch is the caller's.
 // Returns PICTURA_OK with *empty set when there is nothing to render.
-static pictura_status render_setup(pictura_ctx c, const pictura_agents* ag, const pictura_rig* rig,
+static pictura_status render_setup(pictura_ctx c, const pictura_agents* ag, const pictura_rig* rig, int mode,
                                    uint8_t* out_cls, float* out_depth, RenderParams& P, bool* empty)
 {
     *empty = false;
@@ -503,7 +531,7 @@ static pictura_status render_setup(pictura_ctx c, const pictura_agents* ag, cons
         tw = c->tile < P.W ? c->tile : P.W;
         th = c->tile < P.H ? c->tile : P.H;
     } else {
-        choose_tile(V, P.W, P.H, tw, th);
+        choose_tile(V, P.W, P.H, mode, c->lights.lights_per_world > 0, tw, th);
         narrow_tile(V, P.W, P.H, tw, th);
     }
     P.tile_w = tw; P.tile_h = th;
@@ -571,7 +599,7 @@ pictura_status pictura_render_views(pictura_ctx c, const pictura_agents* ag, con
     DeviceGuard dg(c->device);
     RenderParams P;
     bool empty = false;
-    const pictura_status st = render_setup(c, ag, rig, out_cls, out_depth, P, &empty);
+    const pictura_status st = render_setup(c, ag, rig, kModeClass, out_cls, out_depth, P, &empty);
     if (st != PICTURA_OK || empty) return st;
     hipError_t e = render_launch(c, P, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "render_views launch");
@@ -588,7 +616,7 @@ static pictura_status render_rgb(pictura_ctx c, const pictura_agents* ag, const 
     DeviceGuard dg(c->device);
     RenderParams P;
     bool empty = false;
-    const pictura_status st = render_setup(c, ag, rig, out_cls, out_depth, P, &empty);
+    const pictura_status st = render_setup(c, ag, rig, aa ? kModeAA : kModeRgb, out_cls, out_depth, P, &empty);
     if (st != PICTURA_OK || empty) return st;
     P.out_rgb = out_rgb;
     P.rfar = 1.0f / P.farp;
@@ -620,7 +648,7 @@ pictura_status pictura_render_instances(pictura_ctx c, const pictura_agents* ag,
     DeviceGuard dg(c->device);
     RenderParams P;
     bool empty = false;
-    const pictura_status st = render_setup(c, ag, rig, out_cls, out_depth, P, &empty);
+    const pictura_status st = render_setup(c, ag, rig, kModeInst, out_cls, out_depth, P, &empty);
     if (st != PICTURA_OK || empty) return st;
     P.out_inst = out_inst;
     P.out_counts = out_counts;

@@ -40,13 +40,13 @@ def workload(cfg, worlds):
 
 
 SIZES = [(100, 75, 0.3), (80, 45, 0.0), (65, 65, 0.0), (96, 96, 0.0), (120, 67, 0.25), (128, 32, 0.0), (128, 33, 0.0),
-         (68, 64, 0.0), (30, 120, 0.0), (52, 38, 0.0), (61, 7, 0.0), (4, 4, 0.0), (1, 1, 0.0)]
+         (68, 64, 0.0), (30, 120, 0.0), (52, 38, 0.0), (61, 7, 0.0), (4, 4, 0.0), (1, 1, 0.0), (130, 50, 0.0), (136, 76, 0.25)]
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("w, h, shift", SIZES)
 @pytest.mark.parametrize("mode", ["class", "colour", "antialiased", "instances"])
-@pytest.mark.parametrize("worlds", [1, 12])   # tiles cut into columns; whole and (from 6,144 tiles on) wide ones
+@pytest.mark.parametrize("worlds", [1, 12])   # tiles cut into columns; whole and (from 8,192 tiles on) wide ones
 def test_tiles_match_the_oracle(mode, w, h, shift, worlds):
     import torch
     from paper_2607_26005_amd import pictura
@@ -99,3 +99,33 @@ def test_tiles_match_the_oracle(mode, w, h, shift, worlds):
     assert_parity(got_c, got_d, ora, f"{mode} {w}x{h}")
     for k, v in extra.items():
         assert np.array_equal(v, ora[k]), (mode, w, h, k)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode, cfg, w, h, worlds, tiles", [
+    ("class", 3, 96, 96, 12, 4), ("class", 3, 100, 100, 12, 4), ("class", 3, 150, 100, 12, 6),   # 3, 3 and 5 wide ones
+    ("class", 3, 100, 75, 12, 2), ("class", 3, 100, 75, 3, 2), ("instances", 3, 100, 75, 3, 4),   # 12,288 and 3,072 views
+    ("instances", 3, 100, 75, 4, 2), ("class", 3, 130, 50, 12, 2), ("antialiased", 3, 80, 45, 7, 1),
+    ("antialiased", 7, 150, 100, 5, 5), ("class", 7, 96, 96, 16, 3)])   # lights
+def test_wide_tiles_where_they_pay(mode, cfg, w, h, worlds, tiles):
+    import torch
+    from paper_2607_26005_amd import pictura
+    wl = workload(cfg, worlds)
+    mount = np.concatenate([wl.rig.mount] * 2)
+    rig = dataclasses.replace(wl.rig, width=w, height=h, fx=0.6 * w, fy=0.6 * w, cx=w / 2.0, cy=h / 2.0, mount=mount)
+    r = pictura.Renderer(0)
+    try:
+        r.upload(wl.scene, wl.cell_size)
+        if wl.lights is not None:
+            r.set_lights(pictura.DeviceLights.from_host(wl.lights))
+        r.set_option(pictura.OPT_STATS, 1)
+        da = pictura.DeviceAgents.from_host(wl.agents)
+        if mode == "class":
+            r.render(da, rig)
+        elif mode == "instances":
+            r.render_instances(da, rig)
+        else:
+            r.render_rgb(da, rig, antialias=True)
+        assert pictura.pictura_stats_copy(r.ctx)["view_tiles"] == tiles * wl.agents.count * len(mount)
+    finally:
+        r.close_checked()
