@@ -1,8 +1,9 @@
 // Batched class/depth view rasterizer for gfx950.  One workgroup renders one
-// view tile (at most 64x64 pixels) into a framebuffer of 32-bit keys in LDS;
-// the workgroup has kViewWaves waves that share the framebuffer and split the
-// tile's cells and agents between them, each running the whole pipeline on
-// its share with no barrier until the write-out:
+// view tile (64x64 pixels at most, or about as many in a wider or taller one)
+// into a framebuffer of 32-bit keys in LDS; the workgroup has kViewWaves waves
+// that share the framebuffer and split the tile's cells and agents between
+// them, each running the whole pipeline on its share with no barrier until the
+// write-out:
 //
 //  1. cells of the world grid in the rectangle around the tile frustum are
 //     taken 64 at a time (one lane per cell): a cheap test of the cell
@@ -739,91 +740,91 @@ __device__ __forceinline__ void raster_blocks(const RenderParams& P, Shared& S, 
         }
     }
     for (int b0 = 0;; b0 += 64) {
-    // lane b: block b0 + b of the box
-    const int bi = b0 + lane;
-    const int eby = (int)(((uint32_t)bi * rinv) >> 16), ebx = bi - eby * nbx;
-    // (lanes past the box hold no block; the masks keep X and Y small, so the
-    // products below stay 24-bit multiplies)
-    const int X = ((bx0 + ebx) & kMask) * 8, Y = ((by0 + eby) & kMask) * 8;
-    bool pass = bi < nb;
+        // lane b: block b0 + b of the box
+        const int bi = b0 + lane;
+        const int eby = (int)(((uint32_t)bi * rinv) >> 16), ebx = bi - eby * nbx;
+        // (lanes past the box hold no block; the masks keep X and Y small, so the
+        // products below stay 24-bit multiplies)
+        const int X = ((bx0 + ebx) & kMask) * 8, Y = ((by0 + eby) & kMask) * 8;
+        bool pass = bi < nb;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        if constexpr (I32) {
-            off[k] = __mul24(A[k], X) + __mul24(B[k], Y);
-            const int d = 7 * (max(A[k], 0) + max(B[k], 0));
-            pass = pass & ((Cc[k] + d) + off[k] >= 0);
-        } else {
-            off[k] = fma(A[k], (double)X, B[k] * (double)Y);
-            const double d = 7.0 * (fmax(A[k], 0.0) + fmax(B[k], 0.0));
-            pass = pass & ((Cc[k] + d) + off[k] >= 0.0);
+        for (int k = 0; k < 3; ++k) {
+            if constexpr (I32) {
+                off[k] = __mul24(A[k], X) + __mul24(B[k], Y);
+                const int d = 7 * (max(A[k], 0) + max(B[k], 0));
+                pass = pass & ((Cc[k] + d) + off[k] >= 0);
+            } else {
+                off[k] = fma(A[k], (double)X, B[k] * (double)Y);
+                const double d = 7.0 * (fmax(A[k], 0.0) + fmax(B[k], 0.0));
+                pass = pass & ((Cc[k] + d) + off[k] >= 0.0);
+            }
         }
-    }
-    const float pxu = (float)(T.x0 + X), pyu = (float)(T.y0 + Y);
-    const uint32_t xy = (uint32_t)X | ((uint32_t)Y << 8);
-    const uint32_t boff = (uint32_t)((Y * T.pitch + X) * 4);   // byte offset of the block in the framebuffer
-    uint64_t m = __ballot(pass);
-    if (P.stats && lane == 0) {
-        if (b0 == 0) atomicAdd(&S.stat[kStBlocksTested], (uint32_t)nb);
-        atomicAdd(&S.stat[kStBlocksPassed], (uint32_t)__popcll(m));
-    }
-    // Lanes that miss the piece take the key 0xFFFFFFFF, which changes
-    // nothing, so the LDS minimum needs no branch (every address lies inside
-    // the framebuffer: rows below 64, columns below the pitch).
-    auto key_at = [&](int b, uint32_t& addr) -> uint32_t {
-        if constexpr (I32 && Fast) {
-            // the block's offsets, as the lane that tested it computed them
-            // (broadcast through the LDS crossbar: no vector ALU instruction)
-            // (all six fetched before any is used: one LDS round trip per block)
-            const uint32_t ga = bperm(b, boff);
-            const uint32_t g0 = bperm(b, (uint32_t)off[0]), g1 = bperm(b, (uint32_t)off[1]);
-            const uint32_t g2 = bperm(b, (uint32_t)off[2]);
-            const uint32_t gx = bperm(b, __float_as_uint(pxu)), gy = bperm(b, __float_as_uint(pyu));
-            const int e0 = Eb[0] + (int)g0;
-            const int e1 = Eb[1] + (int)g1;
-            const int e2 = Eb[2] + (int)g2;
-            const float pxf = pxl + __uint_as_float(gx);
-            const float pyf = pyl + __uint_as_float(gy);
+        const float pxu = (float)(T.x0 + X), pyu = (float)(T.y0 + Y);
+        const uint32_t xy = (uint32_t)X | ((uint32_t)Y << 8);
+        const uint32_t boff = (uint32_t)((Y * T.pitch + X) * 4);   // byte offset of the block in the framebuffer
+        uint64_t m = __ballot(pass);
+        if (P.stats && lane == 0) {
+            if (b0 == 0) atomicAdd(&S.stat[kStBlocksTested], (uint32_t)nb);
+            atomicAdd(&S.stat[kStBlocksPassed], (uint32_t)__popcll(m));
+        }
+        // Lanes that miss the piece take the key 0xFFFFFFFF, which changes
+        // nothing, so the LDS minimum needs no branch (every address lies inside
+        // the framebuffer: whole blocks, columns below the pitch).
+        auto key_at = [&](int b, uint32_t& addr) -> uint32_t {
+            if constexpr (I32 && Fast) {
+                // the block's offsets, as the lane that tested it computed them
+                // (broadcast through the LDS crossbar: no vector ALU instruction)
+                // (all six fetched before any is used: one LDS round trip per block)
+                const uint32_t ga = bperm(b, boff);
+                const uint32_t g0 = bperm(b, (uint32_t)off[0]), g1 = bperm(b, (uint32_t)off[1]);
+                const uint32_t g2 = bperm(b, (uint32_t)off[2]);
+                const uint32_t gx = bperm(b, __float_as_uint(pxu)), gy = bperm(b, __float_as_uint(pyu));
+                const int e0 = Eb[0] + (int)g0;
+                const int e1 = Eb[1] + (int)g1;
+                const int e2 = Eb[2] + (int)g2;
+                const float pxf = pxl + __uint_as_float(gx);
+                const float pyf = pyl + __uint_as_float(gy);
+                const float iz = fmaf(pa, pxf, fmaf(pb, pyf, pc));
+                const uint32_t key = depth_key(P, iz, cls);
+                addr = ga + (uint32_t)loff4;
+                return (((e0 | e1 | e2) >= 0) && iz >= P.izfar) ? key : 0xFFFFFFFFu;
+            }
+            const uint32_t q = readlane(xy, b);
+            const int bX = (int)(q & 255u), bY = (int)(q >> 8);
+            bool cov;
+            if constexpr (I32) {
+                const int e0 = Eb[0] + (A[0] * bX + B[0] * bY);
+                const int e1 = Eb[1] + (A[1] * bX + B[1] * bY);
+                const int e2 = Eb[2] + (A[2] * bX + B[2] * bY);
+                cov = (e0 | e1 | e2) >= 0;
+            } else {
+                const double e0 = Eb[0] + readlane_d(off[0], b);
+                const double e1 = Eb[1] + readlane_d(off[1], b);
+                const double e2 = Eb[2] + readlane_d(off[2], b);
+                cov = (e0 >= 0.0) & (e1 >= 0.0) & (e2 >= 0.0);
+            }
+            float pxf, pyf;
+            if constexpr (Fast) {
+                pxf = pxl + readlane_f(pxu, b);
+                pyf = pyl + readlane_f(pyu, b);
+            } else {
+                cov = cov & (lx < T.w - bX) & (ly < T.h - bY);
+                pxf = ((float)(T.x0 + bX + lx) + 0.5f) - P.cx;
+                pyf = ((float)(T.y0 + bY + ly) + 0.5f) - P.cy;
+            }
             const float iz = fmaf(pa, pxf, fmaf(pb, pyf, pc));
             const uint32_t key = depth_key(P, iz, cls);
-            addr = ga + (uint32_t)loff4;
-            return (((e0 | e1 | e2) >= 0) && iz >= P.izfar) ? key : 0xFFFFFFFFu;
+            addr = (uint32_t)((bY * T.pitch + bX) * 4 + loff4);
+            return (cov && iz >= P.izfar) ? key : 0xFFFFFFFFu;
+        };
+        while (m) {
+            const int b = __builtin_ctzll(m);
+            m &= m - 1;
+            uint32_t addr;
+            const uint32_t key = key_at(b, addr);
+            atomicMin((uint32_t*)((char*)S.fb + addr), key);
         }
-        const uint32_t q = readlane(xy, b);
-        const int bX = (int)(q & 255u), bY = (int)(q >> 8);
-        bool cov;
-        if constexpr (I32) {
-            const int e0 = Eb[0] + (A[0] * bX + B[0] * bY);
-            const int e1 = Eb[1] + (A[1] * bX + B[1] * bY);
-            const int e2 = Eb[2] + (A[2] * bX + B[2] * bY);
-            cov = (e0 | e1 | e2) >= 0;
-        } else {
-            const double e0 = Eb[0] + readlane_d(off[0], b);
-            const double e1 = Eb[1] + readlane_d(off[1], b);
-            const double e2 = Eb[2] + readlane_d(off[2], b);
-            cov = (e0 >= 0.0) & (e1 >= 0.0) & (e2 >= 0.0);
-        }
-        float pxf, pyf;
-        if constexpr (Fast) {
-            pxf = pxl + readlane_f(pxu, b);
-            pyf = pyl + readlane_f(pyu, b);
-        } else {
-            cov = cov & (lx < T.w - bX) & (ly < T.h - bY);
-            pxf = ((float)(T.x0 + bX + lx) + 0.5f) - P.cx;
-            pyf = ((float)(T.y0 + bY + ly) + 0.5f) - P.cy;
-        }
-        const float iz = fmaf(pa, pxf, fmaf(pb, pyf, pc));
-        const uint32_t key = depth_key(P, iz, cls);
-        addr = (uint32_t)((bY * T.pitch + bX) * 4 + loff4);
-        return (cov && iz >= P.izfar) ? key : 0xFFFFFFFFu;
-    };
-    while (m) {
-        const int b0 = __builtin_ctzll(m);
-        m &= m - 1;
-        uint32_t a0;
-        const uint32_t k0 = key_at(b0, a0);
-        atomicMin((uint32_t*)((char*)S.fb + a0), k0);
-    }
-    if (!kWide || b0 + 64 >= nb) break;
+        if (!kWide || b0 + 64 >= nb) break;
     }
 }
 
@@ -1109,50 +1110,50 @@ __device__ void aa_pieces(const RenderParams& P, Shared& S, WaveLds& L, uint32_t
         const uint32_t rcls = readlane(cls, l);
         // blocks of the window, 8 x 8 of them at a time (not kWide: that is all)
         for (int gj = rj0;; gj += 64) {
-        for (int gi = ri0;; gi += 64) {
-        const int nbx = kWide ? min((ri1 - gi + 8) >> 3, 8) : (ri1 - gi + 8) >> 3;
-        const int nby = kWide ? min((rj1 - gj + 8) >> 3, 8) : (rj1 - gj + 8) >> 3;
-        uint64_t bm = 1;
-        if (nbx * nby > 1) {
-            // lane = block (lx, ly) of the window: does it hold a fragment?
-            bool need = false;
-            if (lx < nbx && ly < nby) {
-                // from the edge function at the block's centre and the most it
-                // changes over the block's pixels, in pixels of distance; 2^-6 and 2^-9
-                // cover the fp32 roundings (of values that matter only below 16)
-                const double ci = (double)(gi + 8 * lx) + 3.5, cj = (double)(gj + 8 * ly) + 3.5;
-                bool out = false, in = true;
+            for (int gi = ri0;; gi += 64) {
+                const int nbx = kWide ? min((ri1 - gi + 8) >> 3, 8) : (ri1 - gi + 8) >> 3;
+                const int nby = kWide ? min((rj1 - gj + 8) >> 3, 8) : (rj1 - gj + 8) >> 3;
+                uint64_t bm = 1;
+                if (nbx * nby > 1) {
+                    // lane = block (lx, ly) of the window: does it hold a fragment?
+                    bool need = false;
+                    if (lx < nbx && ly < nby) {
+                        // from the edge function at the block's centre and the most it
+                        // changes over the block's pixels, in pixels of distance; 2^-6 and 2^-9
+                        // cover the fp32 roundings (of values that matter only below 16)
+                        const double ci = (double)(gi + 8 * lx) + 3.5, cj = (double)(gj + 8 * ly) + 3.5;
+                        bool out = false, in = true;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float mid = (float)fma(rsy[k], cj, fma(rsx[k], ci, re[k]));
-                    const float reach = (float)(fabs(rsx[k]) + fabs(rsy[k])) * (3.5f * 1.001953125f) * rr[k] + 0.515625f;
-                    out = out | (fmaf(mid, rr[k], reach) < 0.0f);
-                    in = in & (fmaf(mid, rr[k], -reach) > 0.0f);
+                        for (int k = 0; k < 4; ++k) {
+                            const float mid = (float)fma(rsy[k], cj, fma(rsx[k], ci, re[k]));
+                            const float reach = (float)(fabs(rsx[k]) + fabs(rsy[k])) * (3.5f * 1.001953125f) * rr[k] + 0.515625f;
+                            out = out | (fmaf(mid, rr[k], reach) < 0.0f);
+                            in = in & (fmaf(mid, rr[k], -reach) > 0.0f);
+                        }
+                        need = !out & !in;
+                    }
+                    bm = __ballot(need);
                 }
-                need = !out & !in;
+                STAT1(kStAaBlocks, __popcll(bm));
+                while (bm) {
+                    const int b = __builtin_ctzll(bm);
+                    bm &= bm - 1;
+                    const int i = gi + 8 * (b & 7) + lx, j = gj + 8 * (b >> 3) + ly;   // tile pixel
+                    const double di = (double)i, dj = (double)j;
+                    uint32_t f;
+                    const bool frag = aa_fragment(P, rq4, aa_cover(fma(rsy[0], dj, fma(rsx[0], di, re[0])), rr[0]),
+                                                  aa_cover(fma(rsy[1], dj, fma(rsx[1], di, re[1])), rr[1]),
+                                                  aa_cover(fma(rsy[2], dj, fma(rsx[2], di, re[2])), rr[2]),
+                                                  aa_cover(fma(rsy[3], dj, fma(rsx[3], di, re[3])), rr[3]),
+                                                  centre_off(P, T.x0 + i, P.cx, P.hx), centre_off(P, T.y0 + j, P.cy, P.hy),
+                                                  rpa, rpb, rpc, rcls, f);
+                    const bool hit = frag & (i <= ri1) & (j <= rj1);
+                    STAT(kStAaFrags, hit ? 1 : 0);
+                    if (hit) atomicMin((uint32_t*)((char*)fbo + (uint32_t)(j * P.W + i) * 4u), f);
+                }
+                if (!kWide || gi + 64 > ri1) break;
             }
-            bm = __ballot(need);
-        }
-        STAT1(kStAaBlocks, __popcll(bm));
-        while (bm) {
-            const int b = __builtin_ctzll(bm);
-            bm &= bm - 1;
-            const int i = gi + 8 * (b & 7) + lx, j = gj + 8 * (b >> 3) + ly;   // tile pixel
-            const double di = (double)i, dj = (double)j;
-            uint32_t f;
-            const bool frag = aa_fragment(P, rq4, aa_cover(fma(rsy[0], dj, fma(rsx[0], di, re[0])), rr[0]),
-                                          aa_cover(fma(rsy[1], dj, fma(rsx[1], di, re[1])), rr[1]),
-                                          aa_cover(fma(rsy[2], dj, fma(rsx[2], di, re[2])), rr[2]),
-                                          aa_cover(fma(rsy[3], dj, fma(rsx[3], di, re[3])), rr[3]),
-                                          centre_off(P, T.x0 + i, P.cx, P.hx), centre_off(P, T.y0 + j, P.cy, P.hy),
-                                          rpa, rpb, rpc, rcls, f);
-            const bool hit = frag & (i <= ri1) & (j <= rj1);
-            STAT(kStAaFrags, hit ? 1 : 0);
-            if (hit) atomicMin((uint32_t*)((char*)fbo + (uint32_t)(j * P.W + i) * 4u), f);
-        }
-        if (!kWide || gi + 64 > ri1) break;
-        }
-        if (!kWide || gj + 64 > rj1) break;
+            if (!kWide || gj + 64 > rj1) break;
         }
     }
 }
@@ -1359,7 +1360,7 @@ __device__ __forceinline__ void exact_pass(const RenderParams& P, Shared& S, Wav
         // hand int32-form records to the view's record ring (both waves drain it at the end)
         const uint64_t md = __ballot(big && e32);
         const uint32_t cap = (uint32_t)(T.h + 7 & ~7) >> 2;   // ring records: four framebuffer rows each
-        if (md != 0 && cap != 0) {
+        if (md != 0) {
             const int l0 = __builtin_ctzll(md);
             uint32_t base = 0;
             if (lane_id() == l0) base = atomicAdd(&S.ctl[kRecTail], (uint32_t)__popcll(md));
