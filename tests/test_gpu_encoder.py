@@ -78,10 +78,12 @@ def _exact(torch, enc, cls, depth):
 
 
 @pytest.mark.parametrize("V, H, W, cams", [(8, 54, 96, 4), (6, 29, 37, 3), (2, 8, 8, 2), (1, 1, 1, 1), (5, 3, 130, 5),
-                                           (4, 130, 130, 4), (4, 64, 64, 2), (3, 121, 8, 1)])
+                                           (4, 130, 130, 4), (4, 64, 64, 2), (3, 121, 8, 1), (2, 128, 128, 2),
+                                           (2, 8, 1928, 1), (2, 1920, 1, 1), (2, 8, 2056, 1)])
 def test_native_encoder_matches_float64(V, H, W, cams):
     # Sizes around the tiles: 256 and 128 output pixels per workgroup, 16
-    # tokens per attention step, and more than 256 tokens (130 x 130: 289).
+    # tokens per attention step; 240, 241 and 256 tokens (the scores take up to
+    # all of 64 KB of LDS) and more, where they are computed again (257, 289).
     torch = _torch()
     from paper_2607_26005_amd.encoder import ViewEncoder
     torch.manual_seed(V * 1000 + H)

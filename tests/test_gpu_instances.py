@@ -173,11 +173,11 @@ def test_instances_largest_view(lib):
 
 
 @pytest.mark.parametrize("res, dist, height", [(64, 3.2, 64), (64, 30.0, 64), (45, 3.2, 37), (45, 9.0, 37), (128, 3.2, 70)])
-def test_instances_ties_between_waves(lib, res, dist, height):
-    # Five identical boxes, dealt to different waves of the workgroup: the
-    # lowest index owns every pixel whichever wave draws first; a sixth box
-    # stands before or inside them.  Near boxes have pieces larger than a packed
-    # step, with clipped triangles; far ones only packed pieces.
+def test_instances_ties_and_pieces(lib, res, dist, height):
+    # Five identical boxes: the lowest index owns every pixel, as the boxes are
+    # drawn in ascending order; a sixth box stands before or inside them.  Near
+    # boxes have pieces larger than a packed step, with clipped triangles, which
+    # are swept one at a time; far ones only packed pieces.
     from tests.scenes import make_agents, make_rig, make_scene, quad
     G = 1000.0
     scene = make_scene(quad((-G, -G, -1.5), (G, -G, -1.5), (G, G, -1.5), (-G, G, -1.5)), [0, 0])
@@ -185,8 +185,8 @@ def test_instances_ties_between_waves(lib, res, dist, height):
     ag = make_agents([(0.0, 0.0, 0.0, 1.0, 0.0, 4.5, 1.9, 1.5, 3)] + [same] * 5
                      + [(0.8 * dist, -0.3, -1.5, 1.0, 0.0, 0.5, 0.5, 1.7, 6)])
     rig = make_rig(res=res, height=height, mounts=((0.0, 0.0, 0.0, 1.0, 0.0), (0.0, 0.0, 0.0, 0.8, 0.6)))
-    wl = sg.Workload("inst-wave-ties", 0, 0, scene, ag, rig, 16.0, 2000.0)
-    check(lib, wl, np.arange(wl.num_views), "inst-wave-ties")
-    check(lib, wl, np.arange(wl.num_views), "inst-wave-ties-64", tile=64)
+    wl = sg.Workload("inst-ties", 0, 0, scene, ag, rig, 16.0, 2000.0)
+    check(lib, wl, np.arange(wl.num_views), "inst-ties")
+    check(lib, wl, np.arange(wl.num_views), "inst-ties-64", tile=64)
     c = O.render(scene, ag, rig, view_ids=[0], want_instances=True)["counts"][0]
     assert c[1, 1] > 0 and (c[2:6, 1] == 0).all() and (c[2:6, 0] == c[1, 0]).all()

@@ -53,11 +53,11 @@ def test_tiles_match_the_oracle(mode, w, h, shift, worlds):
     wl = workload(7 if h % 2 else 3, worlds)   # town with lights, or dense traffic
     if worlds > 1 and (w > 64 or h > 64) and w * h < 16000:   # eight cameras: a launch of wide tiles
         wl = dataclasses.replace(wl, rig=dataclasses.replace(wl.rig, mount=np.concatenate([wl.rig.mount] * 2)))
-        if wl.num_views < 5000:   # (the town has fewer agents: each stands twice in its world)
+        if wl.num_views < 5000:   # (the town has fewer agents: each stands three times in its world)
             a = wl.agents
-            twice = lambda v: np.repeat(v.reshape(a.num_worlds, -1), 3, 0).reshape(-1)
+            thrice = lambda v: np.repeat(v.reshape(a.num_worlds, -1), 3, 0).reshape(-1)
             wl = dataclasses.replace(wl, agents=dataclasses.replace(
-                a, agents_per_world=3 * a.agents_per_world, **{f.name: twice(getattr(a, f.name)) for f in dataclasses.fields(a)
+                a, agents_per_world=3 * a.agents_per_world, **{f.name: thrice(getattr(a, f.name)) for f in dataclasses.fields(a)
                                                                if isinstance(getattr(a, f.name), np.ndarray)}))
     rig = dataclasses.replace(wl.rig, width=w, height=h, fx=0.6 * w, fy=0.6 * w, cx=w / 2.0 + shift,
                               cy=h / 2.0 - shift)
