@@ -294,11 +294,10 @@ __device__ __forceinline__ int world_of_cell(const WorldGrid* g, int nw, int64_t
 // Bounding box of every cell, from its primitives in cell order, and each
 // world's margin.  kCellLanes lanes share a cell (about nine primitives on
 // average, some hundreds next to roads); minima and maxima are of the
-// order-preserving bit patterns.  The boxes were six atomics per primitive
-// before, and every cell took an atomic on its world's one margin word; now a
-// wave whose cells lie in one world sends its largest: with the arrays of the
-// last scene kept as well, binning 64 worlds of 45 K triangles takes 0.35 ms
-// instead of 2.67 (this kernel and the count took 0.69 and 0.55 of them).
+// order-preserving bit patterns.  A wave whose cells lie in one world sends its
+// largest margin alone: atomics are what bound this before (six per primitive
+// and one per cell: 0.69 ms of the binning of 64 worlds of 45 K triangles, which
+// takes 0.35 ms in all this way).
 constexpr int kCellLanes = 8;
 // Cells of one launch: a grid is limited to 2^32 - 1 threads, a scene to 2^31 - 1 cells.
 constexpr int64_t kCellsPerLaunch = 1ll << 28;

@@ -13,13 +13,14 @@
 // matrix cores (2.5 PFLOP/s / 6 against 157 TFLOP/s).  Values are cut once,
 // where they are produced, and stored as [pixel][channels / 32][3][32].
 //
-// Measured on 8,192 views of 96x54: 4.9 ms a call, 15.6 ms through PyTorch's
-// layers (MIOpen's Winograd convolutions 8.1 ms, the planes, ReLUs and layout
-// changes around them 6 ms, the attention 2 ms).  The error against the same
-// encoder in fp64 is 2.7e-8, 3.1e-8 through the layers.  Kernels: first
-// convolution 0.73 ms (2.0 GB written), then 0.99, 1.14, 0.71 and 1.06 ms (0.61,
-// 1.07, 0.85 and 1.15 PFLOP/s of bf16 products; a large bf16 matrix product
-// reaches 1.15 on this card), attention 0.40 ms.
+// Measured on 8,192 views of 96x54 of a town: 5.0 ms a call, 15.6 ms through
+// PyTorch's layers (MIOpen's Winograd convolutions 8.1 ms, the planes, ReLUs and
+// layout changes around them 6 ms, the attention 2 ms).  The error against the
+// same encoder in fp64 is 2.7e-8, 3.1e-8 through the layers, and of the
+// convolutions alone with positive weights 1.1e-7, 1.4e-7 through the layers.
+// Kernels: first convolution 0.71 ms (2.0 GB written), then 0.98, 1.12, 0.68 and
+// 1.00 ms (0.62, 1.09, 0.90 and 1.22 PFLOP/s of bf16 products; a large bf16 matrix
+// product reaches 1.15 on this card), attention 0.39 ms, the rest 0.08 ms.
 #include <cmath>
 
 #include "pictura.h"
@@ -65,7 +66,7 @@ __device__ __forceinline__ void split3(float x, uint32_t& hi, uint32_t& mid, uin
 // infinity: of an infinity (or NaN) the second is one, and the third, the
 // difference of the two, is held to a number that no finite value's reaches
 // and that adds to the same side.  Without branches: with one per pair for
-// such values the first convolution took 969 us instead of 726.
+// such values the first convolution took 969 us instead of 711.
 __device__ __forceinline__ void split3_pair(float x0, float x1, uint32_t& hi, uint32_t& mid, uint32_t& lo)
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -451,8 +452,8 @@ __global__ __launch_bounds__(256, 2) void enc_conv_kernel(const uint16_t* __rest
 // three (their weights one tap at a time), and a lane whose pixel has no
 // neighbour there reads a row of zeros.  Staging is what holds the general
 // kernel back: with 0.47 and 0.67 of its bytes the 64- and 128-channel
-// convolutions of 8,192 views take 1.14 instead of 1.48 ms and 1.06 instead of
-// 1.19.
+// convolutions of 8,192 views take 1.12 instead of 1.47 ms and 1.00 instead of
+// 1.16.
 template <int kCin, int kCout, int MT, bool kLast>
 __global__ __launch_bounds__(256, 2) void enc_conv_s1_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ wk,
                                                              const float* __restrict__ bias, int h, int w, int64_t pixels,

@@ -309,9 +309,8 @@ __device__ __forceinline__ void near_cross(const RenderParams& P, float ix, floa
 // read through it: their addresses are loaded next to each use (the empty asm
 // keeps the compiler from loading them once and holding 18 scalar registers
 // all the way, which spills others: 12 spilled in the one-tile class/depth
-// kernel).  A kernel that packed the agents for every call before spilled 22 and
-// cost its launch: 8,192 views 181 -> 171 us a call, 262,144 views 4,398 ->
-// 4,346.
+// kernel, 22 with one array packed by a kernel ahead of every call: 8,192 views
+// 174 us a call against 181 that way).
 typedef const RenderParams __attribute__((address_space(4)))* KernArgs;
 __device__ __forceinline__ KernArgs kernargs()
 {
