@@ -43,7 +43,7 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E peak
 # `traffic` is reported as null.
 TRAFFIC = {
     "config": 4,
-    "sources_sha256": "b6ab9f13c1bbdadc692e3441d2867c791502438484a0e89202ecf2936475db84",
+    "sources_sha256": "1861e6e0e0c1a4a94b8f4e6ba0aa85d577e1710aa85e0245d17ee356f18cf77a",
     "fetch_bytes": 1.1530e9,
     "write_bytes": 5368709120,
 }

@@ -1739,9 +1739,10 @@ __device__ __forceinline__ void draw_box_instances(const RenderParams& P, Shared
 // lights fold away.  4 as 1 with any tile of at most 64x64: only those paths
 // fold away (8,192 views of 96x54: 271 us against shape 0's 277).  3 any
 // tile, also one wider or taller than 64, whose records and surfaces can have
-// more than 64 blocks: the loops over them cost registers (antialiased 96x54
-// views spill 128 instead of 80 bytes per lane and take 1,011 us instead of
-// 869), so narrower tiles keep the kernels without.
+// more than 64 blocks: the loops over them cost registers (8,192 antialiased
+// views of 96x54 spill 84 instead of 60 bytes per lane and take 649 us instead
+// of 618, class/depth ones 273 instead of 261), so narrower tiles keep the
+// kernels without.
 template <int kMode, bool kDebug, int kShape = 0>
 __global__ __launch_bounds__(kThreads, kWavesPerSimd)
 void render_views_kernel(const RenderParams P_)
